@@ -21,10 +21,12 @@
 //    waves, s = amax / 448 (IEEE division),
 //    q = RN(x / s) computed with one reciprocal per block and a remainder
 //    correction for bf16 sources (exact in the range that reaches E4M3;
-//    checked for every bf16 input pair), IEEE division otherwise, then
-//    v_cvt_pk_fp8_f32. The scale is written by thread 0.
+//    checked for every bf16 input pair), two for fp32 ones, IEEE division
+//    outside those forms' range, then v_cvt_pk_fp8_f32. The scale is written by thread 0.
 // The work is bandwidth bound: no matrix cores are involved.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "wb_internal.hpp"
 
@@ -68,6 +70,12 @@ __device__ __forceinline__ void st(T v, T* p) {
 #else
   *p = v;
 #endif
+}
+
+// A table's address as a pointer to global memory, so that accesses through
+// it need no check for the LDS aperture (flat instructions).
+__device__ __forceinline__ char* global_ptr(uint64_t p) {
+  return (char*)reinterpret_cast<__attribute__((address_space(1))) char*>(p);
 }
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -414,6 +422,16 @@ __device__ __forceinline__ float load_f32(const char* p, int dt) {
   return dt == WB_F32 ? *reinterpret_cast<const float*>(p) : __uint_as_float(uint32_t(*reinterpret_cast<const uint16_t*>(p)) << 16);
 }
 
+// Address of element (r, c) of the block in its pieces of es-byte elements.
+__device__ __forceinline__ const char* find_one(const QPiece* pcs, uint32_t n, const char* recv, int r, int c, int es) {
+  for (uint32_t i = 0; i < n; ++i) {
+    const QPiece& p = pcs[i];
+    if (r >= p.r0 && r <= p.r1m1 && c >= p.c0 && c <= p.c1m1)
+      return recv + p.src_off + (uint64_t(r - p.r0) * p.src_ld + (c - p.c0)) * es;
+  }
+  return nullptr;
+}
+
 // Element (r, c) of the block from its pieces (the block is exactly covered).
 __device__ __forceinline__ float gather_one(const QPiece* pcs, int n, const char* recv, int r, int c) {
   for (int i = 0; i < n; ++i) {
@@ -447,8 +465,16 @@ constexpr int kLdsPieces = 128;
 //   it in the correction. Since |x| <= amax, |q| <= 448.00003 rounds to at most
 //   448 in E4M3, so no clamp is needed. Both are verified exhaustively for
 //   every bf16 (x, amax) pair.
-// mode 0 (fp32 sources, subnormal s): IEEE division, clamped to +-448 (a no-op
-//   that keeps the conversion away from its overflow path whatever the source).
+// mode 3 (fp32 source, -90 <= E <= 100, m not all ones): the same with a
+//   second correction: q0 = RN(x r) is within 2 ulp, q1 = RN(q0 + e0 r) then
+//   within 1, and for such a q1, r = RN(1 / s) and e1 = x - q1 s (exact)
+//   RN(q1 + e1 r) is RN(x / s) (Markstein's theorem, which excludes an s whose
+//   significand is all ones). Where |x / s| < 2^-11 the steps may underflow;
+//   the result then still rounds to zero. 6 operations instead of the about
+//   12 of a division. Clamped like mode 0, so a NaN gives what it gave there.
+// mode 0 (other fp32 sources, subnormal s): IEEE division, clamped to +-448 (a
+//   no-op that keeps the conversion away from its overflow path whatever the
+//   source).
 struct QScale {
   float s, sp, rp, pw;
   int mode;
@@ -459,7 +485,8 @@ __device__ __forceinline__ QScale make_scale(float amax, bool bf16_source) {
   q.s = amax > 0.0f ? amax / 448.0f : 1.0f;  // IEEE fp32 division
   const uint32_t sbits = __float_as_uint(q.s);
   const int sexp = int((sbits >> 23) & 0xFF);  // E + 127
-  q.mode = (!bf16_source || sexp == 0) ? 0 : (sexp >= 127 - 90 && sexp <= 127 + 100) ? 2 : 1;
+  const bool mid = sexp >= 127 - 90 && sexp <= 127 + 100;
+  q.mode = sexp == 0 ? 0 : bf16_source ? (mid ? 2 : 1) : (mid && (sbits & 0x007FFFFFu) != 0x007FFFFFu) ? 3 : 0;
   q.pw = __uint_as_float(uint32_t(254 - sexp) << 23);  // 2^-E
   q.sp = q.mode == 1 ? __uint_as_float((sbits & 0x007FFFFFu) | 0x3F800000u) : q.s;  // m, or s
   q.rp = 1.0f / q.sp;
@@ -469,6 +496,12 @@ __device__ __forceinline__ QScale make_scale(float amax, bool bf16_source) {
 template <int kMode>
 __device__ __forceinline__ float quotient(float x, const QScale& q) {
   if (kMode == 0) return __builtin_amdgcn_fmed3f(x / q.s, -448.0f, 448.0f);
+  if (kMode == 3) {
+    const float q0 = x * q.rp;
+    const float q1 = fmaf(fmaf(-q0, q.s, x), q.rp, q0);
+    const float q2 = fmaf(fmaf(-q1, q.s, x), q.rp, q1);
+    return __builtin_amdgcn_fmed3f(__builtin_copysignf(q2, x), -448.0f, 448.0f);
+  }
   const float xp = kMode == 1 ? x * q.pw : x;
   const float q0 = xp * q.rp;
   const float e = fmaf(-q0, q.sp, xp);
@@ -572,7 +605,7 @@ __device__ __forceinline__ void qblock_pair_run(const PairLane& L, const PairBan
             base = S.base[j];
             ld2 = S.ld2[j];
           }
-        raw[k] = ld(reinterpret_cast<const u32x4*>(base + uint64_t(r) * ld2 + uint64_t(cg) * 2));
+        raw[k] = ld(reinterpret_cast<const u32x4*>(global_ptr(base + uint64_t(r) * ld2 + uint64_t(cg) * 2)));
       }
     }
   } else if (kFull) {
@@ -619,7 +652,7 @@ __device__ __forceinline__ void qblock_pair_run(const PairLane& L, const PairBan
   quantise_block<R, kStep>([&](int k, float* v) { unpack8(raw[k], v); }, qs, rows, cols, rb, cg, L.q8, L.dst_ld,
                            kFull || L.vec);
   const QBlock& b = h ? b1 : b0;
-  if (on && (threadIdx.x & ~16u) == 0) reinterpret_cast<float*>(ptrs[b.scale_idx])[b.scale_off] = qs.s;
+  if (on && (threadIdx.x & ~16u) == 0) reinterpret_cast<float*>(global_ptr(ptrs[b.scale_idx]))[b.scale_off] = qs.s;
 }
 
 // This lane's view of the block it works on in a pair (h: 0 or 1).
@@ -631,8 +664,8 @@ __device__ __forceinline__ PairLane pair_lane(const QBlock& b0, const QBlock& b1
   L.src_ld2 = uint64_t(b.src_ld) * 2;
   L.src = recv + b.src_off + uint64_t(cg) * 2 + uint64_t(rb) * L.src_ld2;
   L.dst_ld = b.dst_ld;
-  uint8_t* const q0 = reinterpret_cast<uint8_t*>(ptrs[b0.dst_idx]) + b0.dst_off;
-  uint8_t* const q1 = reinterpret_cast<uint8_t*>(ptrs[b1.dst_idx]) + b1.dst_off;
+  uint8_t* const q0 = reinterpret_cast<uint8_t*>(global_ptr(ptrs[b0.dst_idx])) + b0.dst_off;
+  uint8_t* const q1 = reinterpret_cast<uint8_t*>(global_ptr(ptrs[b1.dst_idx])) + b1.dst_off;
   L.q8 = h ? q1 : q0;
   L.rows = on ? b.rows_m1 + 1 : 0;
   L.cols = b.cols_m1 + 1;
@@ -701,92 +734,246 @@ __device__ __forceinline__ void qblock_pair(const QBlock* __restrict__ blocks, u
   }
 }
 
-// One block of any kind (several wire pieces, unaligned or fp32 ones): thread t
-// holds columns 8 (t mod 16) .. + 7 of rows t / 16 + 16 k, k < 8, as fp32,
-// gathered from the pieces.
-__device__ __forceinline__ void qblock_one(const QBlock& b, const QPiece* __restrict__ pieces, const uint64_t* __restrict__ ptrs,
-                           const char* recv) {
-  constexpr int R = 8, kStep = 16;
-  static_assert(kQBlockThreads == 16 * kStep, "block mapping");
-  __shared__ float wave_max[kQBlockThreads / 64];
-  __shared__ QPiece lds_pcs[kLdsPieces];
-  __shared__ uint8_t row_piece[128];
-  const int rows = b.rows_m1 + 1, cols = b.cols_m1 + 1;
-  const int cg = (threadIdx.x & 15) * 8, rb = threadIdx.x >> 4;
-  // stage the piece list in LDS with a row -> piece table for the pieces that
-  // span the block's full width (row bands: the common case, a replicated
-  // tensor split by rows among its senders); resolve each row chunk's source
-  // first (the table, else a search of the list), then issue the loads
-  const int n = b.npieces;
-  const QPiece* pcs = pieces + b.piece0;
-  bool table = false;
-  if (n <= kLdsPieces) {
-    for (int i = threadIdx.x; i < n; i += kQBlockThreads) lds_pcs[i] = pcs[i];
-    for (int r = threadIdx.x; r < 128; r += kQBlockThreads) row_piece[r] = 0xFF;
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += kQBlockThreads) {
-      const QPiece& p = lds_pcs[i];
-      if (p.c0 == 0 && p.c1m1 == cols - 1)
-        for (int r = p.r0; r <= p.r1m1; ++r) row_piece[r] = static_cast<uint8_t>(i);
-    }
-    __syncthreads();
-    pcs = lds_pcs;
-    table = true;
-  }
-  const char* src[R];
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    const int r = rb + kStep * k;
-    src[k] = nullptr;
-    if (r >= rows || cg >= cols) continue;
-    int i = table ? row_piece[r] : 0xFF;
+// Vectors at element alignment: gfx950 loads and stores global memory at any
+// byte address, so an unaligned chunk costs the same instruction.
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef u32x2 u32x2_a1 __attribute__((aligned(1)));
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
+
+// Where the 16-byte chunks of the block's rows come from: a block that is
+// one wire piece (QB_DIRECT) keeps its address in the descriptor; otherwise
+// the piece list is staged in LDS with a row -> piece table for the pieces
+// that span the block's full width (row bands: a replicated tensor split by
+// rows among its senders, a flat shard cut between rows). Rows with none
+// search the list.
+enum SourceKind { kSourceDirect, kSourceStaged, kSourceList };
+template <int kKind>
+struct BlockSource {
+  const char* base;          // direct: the block's first element
+  const QPiece* pcs;         // staged: in LDS; list: in memory
+  const uint8_t* row_piece;  // staged
+  uint32_t ld, n;
+  template <bool kF32>
+  __device__ __forceinline__ const char* at(const char* recv, int r, int c) const {
+    constexpr int es = kF32 ? 4 : 2, V = 16 / es;
+    if (kKind == kSourceDirect) return base + (uint64_t(r) * ld + c) * es;
+    uint32_t i = kKind == kSourceStaged ? row_piece[r] : 0xFF;
     if (i == 0xFF)
       for (i = 0; i < n; ++i) {
         const QPiece& p = pcs[i];
-        if (r >= p.r0 && r <= p.r1m1 && cg >= p.c0 && cg + 7 <= p.c1m1) break;
+        if (r >= p.r0 && r <= p.r1m1 && c >= p.c0 && c + V - 1 <= p.c1m1) break;
       }
-    if (i < n) {
-      const QPiece& p = pcs[i];
-      const char* a = recv + p.src_off + (uint64_t(r - p.r0) * p.src_ld + (cg - p.c0)) * 2;
-      if (p.sdt == WB_BF16 && cg + 7 <= p.c1m1 && (reinterpret_cast<uintptr_t>(a) & 15) == 0) src[k] = a;
-    }
+    if (i >= n) return nullptr;  // the chunk straddles pieces
+    const QPiece& p = pcs[i];
+    return recv + p.src_off + (uint64_t(r - p.r0) * p.src_ld + (c - p.c0)) * es;
   }
+  template <bool kF32>
+  __device__ __forceinline__ const char* one(const char* recv, int r, int c) const {
+    constexpr int es = kF32 ? 4 : 2;
+    if (kKind == kSourceDirect) return base + (uint64_t(r) * ld + c) * es;
+    return find_one(pcs, n, recv, r, c, es);
+  }
+};
+
+// One block of any kind: a thread holds 16-byte chunks of V wire elements (8
+// bf16 or 4 fp32) of up to R rows, T threads a row (fewer for blocks of at
+// most half or a quarter of 128 columns). A row of 128 is 256 (512) contiguous
+// bytes of a load instruction; sources may sit at any element address and the
+// fp8 rows at any byte. The last chunk of a row whose width is no multiple of
+// V is moved left over its neighbour (the same values, written twice).
+// Bound: HBM; 8 (16) 16-byte loads per thread are in flight at once. An fp32
+// rank of half an 8 B dense model (7.0 GB of blocks in, 1.7 GB out): 8.22 ms when
+// every element searched its piece, 1.56 ms now (5.6 TB/s). For bf16, chunks of
+// 4 elements on 32 threads a row made blocks of 32 row bands 6 % slower than
+// 8 on 16: twice the row lookups.
+template <bool kF32, int kKind>
+__device__ __forceinline__ void qblock_wide(const QBlock& b, const BlockSource<kKind>& S, const uint64_t* __restrict__ ptrs,
+                                            const char* recv) {
+  constexpr int es = kF32 ? 4 : 2, V = 16 / es, T0 = kF32 ? 5 : 4, R = 128 >> (8 - T0);
+  static_assert(kQBlockThreads == 256 && (V << T0) == 128 && (R << (8 - T0)) == 128, "block mapping");
+  __shared__ float wave_max[kQBlockThreads / 64];
+  const int rows = b.rows_m1 + 1, cols = b.cols_m1 + 1;
+  const int sh = cols > 64 ? T0 : cols > 32 ? T0 - 1 : T0 - 2;  // log2 T
+  const int step = kQBlockThreads >> sh, rb = threadIdx.x >> sh;
+  const int c0 = int(threadIdx.x & ((1u << sh) - 1u)) * V;
+  const bool on = c0 < cols;
+  const int cg = min(c0, max(cols - V, 0));
+  const bool whole = cols >= V;
   u32x4 raw[R];
+  bool odd = false;  // some chunk of this lane needs single elements
 #pragma unroll
   for (int k = 0; k < R; ++k) {
+    const int r = rb + step * k;
     raw[k] = u32x4{0u, 0u, 0u, 0u};
-    if (src[k]) raw[k] = ld(reinterpret_cast<const u32x4*>(src[k]));
+    if (!on || r >= rows) continue;
+    const char* p = whole ? S.template at<kF32>(recv, r, cg) : nullptr;
+    if (p)
+      raw[k] = ld(reinterpret_cast<const u32x4_a2*>(p));
+    else
+      odd = true;
   }
-  float v[R][8];
+  if (odd) {
 #pragma unroll
-  for (int k = 0; k < R; ++k) {
-    unpack8(raw[k], v[k]);
-    const int r = rb + kStep * k;
-    if (!src[k] && r < rows && cg < cols) {
+    for (int k = 0; k < R; ++k) {
+      const int r = rb + step * k;
+      if (r >= rows || (whole && S.template at<kF32>(recv, r, cg))) continue;
+      uint32_t e[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int m = 0; m < 8; ++m) v[k][m] = cg + m < cols ? gather_one(pcs, n, recv, r, cg + m) : 0.0f;
+      for (int m = 0; m < V; ++m) {
+        if (cg + m >= cols) break;
+        const char* p = S.template one<kF32>(recv, r, cg + m);
+        if (!p) continue;
+        if (kF32)
+          e[m & 3] = *reinterpret_cast<const uint32_t*>(p);
+        else
+          e[m >> 1] |= uint32_t(*reinterpret_cast<const uint16_t*>(p)) << (16 * (m & 1));
+      }
+      raw[k] = u32x4{e[0], e[1], e[2], e[3]};
     }
   }
+  auto values = [&](int k, float* v) {
+    if (kF32) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) v[m] = __uint_as_float(raw[k][m]);
+    } else {
+      unpack8(raw[k], v);
+    }
+  };
   float amax = 0.0f;
 #pragma unroll
-  for (int k = 0; k < R; ++k)
+  for (int k = 0; k < R; ++k) {
+    float v[V];
+    values(k, v);
 #pragma unroll
-    for (int m = 0; m < 8; ++m) amax = fmaxf(amax, fabsf(v[k][m]));
+    for (int m = 0; m < V; ++m) amax = fmaxf(amax, fabsf(v[m]));
+  }
   for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = amax;
   __syncthreads();
   amax = wave_max[0];
 #pragma unroll
   for (int w = 1; w < kQBlockThreads / 64; ++w) amax = fmaxf(amax, wave_max[w]);
-  const QScale qs = make_scale(amax, (b.flags & QB_BF16_SOURCE) != 0);
-  uint8_t* q8 = reinterpret_cast<uint8_t*>(ptrs[b.dst_idx]) + b.dst_off;
-  quantise_block<R, kStep>(
+  const QScale qs = make_scale(amax, !kF32);
+  if (threadIdx.x == 0) reinterpret_cast<float*>(global_ptr(ptrs[b.scale_idx]))[b.scale_off] = qs.s;
+  if (!on) return;
+  uint8_t* q8 = reinterpret_cast<uint8_t*>(global_ptr(ptrs[b.dst_idx])) + b.dst_off + cg;
+  auto store = [&](auto mode) {
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int r = rb + step * k;
+      if (r >= rows) continue;
+      float v[V], q[V];
+      values(k, v);
+#pragma unroll
+      for (int m = 0; m < V; ++m) q[m] = quotient<mode.value>(v[m], qs);
+      uint32_t w[V / 4];
+#pragma unroll
+      for (int m = 0; m < V / 4; ++m) {
+        w[m] = __builtin_amdgcn_cvt_pk_fp8_f32(q[4 * m], q[4 * m + 1], 0, false);
+        w[m] = __builtin_amdgcn_cvt_pk_fp8_f32(q[4 * m + 2], q[4 * m + 3], w[m], true);
+      }
+      uint8_t* dst = q8 + uint64_t(r) * b.dst_ld;
+      if (!whole) {
+#pragma unroll
+        for (int m = 0; m < V; ++m)
+          if (m < cols) dst[m] = static_cast<uint8_t>(w[m / 4] >> (8 * (m & 3)));
+      } else if (kF32) {
+        st(w[0], reinterpret_cast<u32_a1*>(dst));
+      } else {
+        st(u32x2{w[0], w[V / 4 - 1]}, reinterpret_cast<u32x2_a1*>(dst));
+      }
+    }
+  };
+  // the mode is uniform over the block
+  if (kF32) {
+    if (qs.mode == 3)
+      store(std::integral_constant<int, 3>{});
+    else
+      store(std::integral_constant<int, 0>{});
+  } else if (qs.mode == 2) {
+    store(std::integral_constant<int, 2>{});
+  } else if (qs.mode == 1) {
+    store(std::integral_constant<int, 1>{});
+  } else {
+    store(std::integral_constant<int, 0>{});
+  }
+}
+
+// A block whose pieces are neither all bf16 nor all fp32: element by element
+// from the piece list, 8 rows of 8 columns per thread.
+__device__ void qblock_mixed(const QBlock& b, const QPiece* __restrict__ pieces, const uint64_t* __restrict__ ptrs,
+                             const char* recv) {
+  constexpr int R = 8, kStep = 16;
+  static_assert(kQBlockThreads == 16 * kStep, "block mapping");
+  __shared__ float wave_max[kQBlockThreads / 64];
+  const int rows = b.rows_m1 + 1, cols = b.cols_m1 + 1;
+  const int cg = (threadIdx.x & 15) * 8, rb = threadIdx.x >> 4;
+  float v[R][8], amax = 0.0f;
+#pragma unroll
+  for (int k = 0; k < R; ++k)
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int r = rb + kStep * k;
+      v[k][m] = r < rows && cg + m < cols ? gather_one(pieces + b.piece0, b.npieces, recv, r, cg + m) : 0.0f;
+      amax = fmaxf(amax, fabsf(v[k][m]));
+    }
+  for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = amax;
+  __syncthreads();
+  amax = wave_max[0];
+#pragma unroll
+  for (int w = 1; w < kQBlockThreads / 64; ++w) amax = fmaxf(amax, wave_max[w]);
+  const QScale qs = make_scale(amax, true);
+  QScale q0 = qs;
+  q0.mode = 0;
+  uint8_t* q8 = reinterpret_cast<uint8_t*>(global_ptr(ptrs[b.dst_idx])) + b.dst_off;
+  quantise_store<0, R, kStep>(
       [&](int k, float* out) {
 #pragma unroll
         for (int m = 0; m < 8; ++m) out[m] = v[k][m];
       },
-      qs, rows, cols, rb, cg, q8, b.dst_ld, (b.flags & QB_VEC_STORE) != 0);
-  if (threadIdx.x == 0) reinterpret_cast<float*>(ptrs[b.scale_idx])[b.scale_off] = qs.s;
+      q0, rows, cols, rb, cg, q8, b.dst_ld, (b.flags & QB_VEC_STORE) != 0);
+  if (threadIdx.x == 0) reinterpret_cast<float*>(global_ptr(ptrs[b.scale_idx]))[b.scale_off] = qs.s;
+}
+
+__device__ __forceinline__ void qblock_one(const QBlock& b, const QPiece* __restrict__ pieces, const uint64_t* __restrict__ ptrs,
+                           const char* recv) {
+  __shared__ QPiece lds_pcs[kLdsPieces];
+  __shared__ uint8_t row_piece[128];
+  if (!(b.flags & (QB_BF16_SOURCE | QB_F32_SOURCE))) {
+    qblock_mixed(b, pieces, ptrs, recv);
+    return;
+  }
+  const bool f32 = (b.flags & QB_F32_SOURCE) != 0;
+  const uint32_t n = b.npieces;
+  if (b.flags & QB_DIRECT) {
+    const BlockSource<kSourceDirect> S{recv + b.src_off, nullptr, nullptr, b.src_ld, 0u};
+    if (f32)
+      qblock_wide<true>(b, S, ptrs, recv);
+    else
+      qblock_wide<false>(b, S, ptrs, recv);
+  } else if (n <= kLdsPieces) {  // at least one piece
+    for (uint32_t i = threadIdx.x; i < n; i += kQBlockThreads) lds_pcs[i] = pieces[b.piece0 + i];
+    if (threadIdx.x < 128) row_piece[threadIdx.x] = 0xFF;
+    __syncthreads();
+    // 256 / n threads per piece mark its rows
+    const uint32_t i = threadIdx.x % n, part = threadIdx.x / n, parts = kQBlockThreads / n;
+    const QPiece& p = lds_pcs[i];
+    if (part < parts && p.c0 == 0 && p.c1m1 == b.cols_m1)
+      for (uint32_t r = p.r0 + part; r <= p.r1m1; r += parts) row_piece[r] = static_cast<uint8_t>(i);
+    __syncthreads();
+    const BlockSource<kSourceStaged> S{nullptr, lds_pcs, row_piece, 0u, n};
+    if (f32)
+      qblock_wide<true>(b, S, ptrs, recv);
+    else
+      qblock_wide<false>(b, S, ptrs, recv);
+  } else {
+    const BlockSource<kSourceList> S{nullptr, pieces + b.piece0, nullptr, 0u, n};
+    if (f32)
+      qblock_wide<true>(b, S, ptrs, recv);
+    else
+      qblock_wide<false>(b, S, ptrs, recv);
+  }
 }
 
 }  // namespace
@@ -808,7 +995,8 @@ __global__ __launch_bounds__(kQBlockThreads) void wb_qblock_kernel(const QBlock*
   } else if (blockIdx.x < g0 + g1) {
     qblock_pair(blocks + nfull, 2 * (blockIdx.x - g0), npair - nfull, pieces, ptrs, recv);
   } else {
-    const uint32_t i = npair + (blockIdx.x - g0 - g1);
+    // in XCD-aware order too: blocks of one wire row band are neighbours
+    const uint32_t i = npair + uint32_t(xcd_order(blockIdx.x - g0 - g1, n - npair, kXcdRunPairs));
     if (i < n) qblock_one(blocks[i], pieces, ptrs, recv);
   }
 }

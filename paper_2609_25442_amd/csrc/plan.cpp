@@ -363,19 +363,20 @@ void qlocal_blocks(const wb_layout_t& trainer, const Rank& R, const wb_plan_t& P
         pc.c0 = static_cast<uint8_t>(b0 - bj * B);
         pc.c1m1 = static_cast<uint8_t>(b1 - bj * B - 1);
         pc.sdt = static_cast<uint8_t>(sdt);
-        const bool single = sdt == WB_BF16 && a0 == bi * B && b0 == bj * B && a1 - a0 == rows && b1 - b0 == cols &&
-                            cols % 8 == 0 && pc.src_off % 16 == 0 && (uint64_t(C) * 2) % 16 == 0;
-        fn((sp.e * nbr + bi) * nbc + bj, pc, single, (a1 - a0) * (b1 - b0));
+        const bool whole = a0 == bi * B && b0 == bj * B && a1 - a0 == rows && b1 - b0 == cols;
+        const bool single = whole && sdt == WB_BF16 && cols % 8 == 0 && pc.src_off % 16 == 0 && (uint64_t(C) * 2) % 16 == 0;
+        const uint8_t how = single ? QB_SINGLE : !whole ? 0 : sdt == WB_F32 ? QB_DIRECT | QB_F32_SOURCE : QB_DIRECT;
+        fn((sp.e * nbr + bi) * nbc + bj, pc, how, (a1 - a0) * (b1 - b0));
       }
   };
   for (size_t i = 0; i < nspans; ++i)
-    for_pieces(spans[i], [&](int64_t id, const QPiece& pc, bool single, int64_t a) {
+    for_pieces(spans[i], [&](int64_t id, const QPiece& pc, uint8_t how, int64_t a) {
       S.area[id] += a;
       if (S.round[id] >= 0 && S.round[id] != spans[i].g->round) fail(WB_EINVAL, "internal: fp8 block spans rounds");
       S.round[id] = spans[i].g->round;
-      if (single) {
+      if (how) {
         QBlock& b = S.blocks[id];
-        b.flags |= QB_SINGLE;
+        b.flags |= how;
         b.src_off = pc.src_off;
         b.src_ld = pc.src_ld;
       } else {
@@ -387,8 +388,8 @@ void qlocal_blocks(const wb_layout_t& trainer, const Rank& R, const wb_plan_t& P
   {
     std::vector<uint32_t> fill(S.count.begin(), S.count.end() - 1);
     for (size_t i = 0; i < nspans; ++i)
-      for_pieces(spans[i], [&](int64_t id, const QPiece& pc, bool single, int64_t) {
-        if (!single) S.pieces[fill[id]++] = pc;
+      for_pieces(spans[i], [&](int64_t id, const QPiece& pc, uint8_t how, int64_t) {
+        if (!how) S.pieces[fill[id]++] = pc;
       });
   }
   for (int64_t e = 0; e < l.batch; ++e)
@@ -410,9 +411,13 @@ void qlocal_blocks(const wb_layout_t& trainer, const Rank& R, const wb_plan_t& P
         b.rows_m1 = static_cast<uint8_t>(rows - 1);
         b.cols_m1 = static_cast<uint8_t>(cols - 1);
         if (b.dst_off % 8 == 0 && l.cols % 8 == 0 && cols % 8 == 0) b.flags |= QB_VEC_STORE;
-        bool bf16 = true;
-        for (uint32_t i = p0; i < p0 + np; ++i) bf16 = bf16 && S.pieces[i].sdt == WB_BF16;
+        bool bf16 = !(b.flags & QB_F32_SOURCE), f32 = np > 0;
+        for (uint32_t i = p0; i < p0 + np; ++i) {
+          bf16 = bf16 && S.pieces[i].sdt == WB_BF16;
+          f32 = f32 && S.pieces[i].sdt == WB_F32;
+        }
         if (bf16) b.flags |= QB_BF16_SOURCE;
+        if (f32) b.flags |= QB_F32_SOURCE;
         // row bands: every piece spans the block's width, 16-byte aligned
         // rows; sorted by first row they tile the block from row 0
         if (bf16 && np >= 2 && np <= uint32_t(kMaxBands) && cols % 8 == 0) {
@@ -751,8 +756,18 @@ void check_work(const wb_plan_t& P, const Rank& R) {
         fail(WB_EINVAL, "internal: misaligned single-piece fp8 block");
       inside(0, b.src_off, ((rows - 1) * b.src_ld + cols) * 2, "fp8 single-piece source");
     }
-    if (uint64_t(b.piece0) + b.npieces > P.qpieces.size() || (b.npieces == 0) != ((b.flags & QB_SINGLE) != 0))
+    if (b.flags & QB_DIRECT) {
+      if (b.flags & QB_SINGLE) fail(WB_EINVAL, "internal: fp8 block kinds");
+      inside(0, b.src_off, ((rows - 1) * b.src_ld + cols) * (b.flags & QB_F32_SOURCE ? 4 : 2), "fp8 direct source");
+    }
+    if ((b.flags & QB_BF16_SOURCE) && (b.flags & QB_F32_SOURCE)) fail(WB_EINVAL, "internal: fp8 source types");
+    if (uint64_t(b.piece0) + b.npieces > P.qpieces.size() ||
+        (b.npieces == 0) != ((b.flags & (QB_SINGLE | QB_DIRECT)) != 0))
       fail(WB_EINVAL, "internal: fp8 block pieces out of range");
+    for (uint32_t i = b.piece0; i < b.piece0 + b.npieces; ++i)
+      if (((b.flags & QB_BF16_SOURCE) && P.qpieces[i].sdt != WB_BF16) ||
+          ((b.flags & QB_F32_SOURCE) && P.qpieces[i].sdt != WB_F32))
+        fail(WB_EINVAL, "internal: fp8 source types");
     if (b.npieces && (b.piece0 < P.round_qpieces[2 * k] || b.piece0 + b.npieces > P.round_qpieces[2 * k + 1]))
       fail(WB_EINVAL, "internal: fp8 block pieces outside its round's piece range");
     if (b.flags & QB_BANDS) {

@@ -223,14 +223,14 @@ struct TaskSplit {
 };
 
 // One fp8 destination block and the wire pieces that fill it. Blocks filled by
-// a single 16-byte aligned bf16 piece (QB_SINGLE) carry its source address
-// here and have no piece-table entry, so the kernel needs no piece lookups
-// for them.
+// a single piece carry its source address here and have no piece-table entry,
+// so the kernel needs no piece lookups for them: QB_SINGLE a 16-byte aligned
+// bf16 piece, QB_DIRECT any other one.
 struct QBlock {
   uint64_t dst_off;     // bytes from the fp8 tensor to the block origin
-  uint64_t src_off;     // QB_SINGLE: bytes from recv_buf to the block's first element
-  uint32_t src_ld;      // QB_SINGLE: wire row length in elements
-  uint32_t piece0;      // first piece (npieces is 0 for QB_SINGLE blocks)
+  uint64_t src_off;     // QB_SINGLE, QB_DIRECT: bytes from recv_buf to the block's first element
+  uint32_t src_ld;      // QB_SINGLE, QB_DIRECT: wire row length in elements
+  uint32_t piece0;      // first piece (npieces is 0 for QB_SINGLE and QB_DIRECT blocks)
   uint32_t dst_ld;      // row stride of the fp8 matrix (elements = bytes)
   uint32_t scale_off;   // element index of the block's scale
   uint16_t npieces, dst_idx, scale_idx;
@@ -253,8 +253,16 @@ static_assert(sizeof(QPiece) == 24, "QPiece layout");
 
 // QB_BANDS: a block filled by 2..kMaxBands full-width, aligned bf16 row bands
 // (its pieces, sorted by first row); such blocks take the pair path too, each
-// row loaded from the band that holds it.
-enum QBlockFlags : uint8_t { QB_VEC_STORE = 1, QB_BF16_SOURCE = 2, QB_SINGLE = 4, QB_BANDS = 8 };
+// row loaded from the band that holds it. QB_BF16_SOURCE, QB_F32_SOURCE: every
+// piece is bf16, fp32.
+enum QBlockFlags : uint8_t {
+  QB_VEC_STORE = 1,
+  QB_BF16_SOURCE = 2,
+  QB_SINGLE = 4,
+  QB_BANDS = 8,
+  QB_DIRECT = 16,
+  QB_F32_SOURCE = 32
+};
 constexpr int kMaxBands = 4;
 inline bool qblock_pairable(const QBlock& b) { return (b.flags & (QB_SINGLE | QB_BANDS)) != 0; }
 inline bool qblock_full_single(const QBlock& b) {
@@ -267,7 +275,7 @@ inline bool qblock_full_single(const QBlock& b) {
 // QB_BANDS) up to npair, each pair taken by one workgroup (horizontal
 // neighbours in block order, so one row of the pair is 512 contiguous bytes
 // of the wire), 16 rows of 8 columns per thread; the other blocks follow, one
-// per workgroup, 8 rows of 8 columns per thread.
+// per workgroup, 16 bytes of up to 8 (bf16) or 16 (fp32) rows per thread.
 constexpr int kQBlockThreads = 256;
 inline uint32_t qblock_workgroups(uint32_t n, uint32_t nfull, uint32_t npair) {
   return nfull / 2 + (npair - nfull + 1) / 2 + (n - npair);
