@@ -6,8 +6,8 @@
 //
 //  * wb_tasks_kernel  -- copy/cast work items: 16-byte vectorised row copies,
 //    fp32 -> bf16 (v_cvt_pk_bf16_f32, round to nearest even), bf16 -> fp32,
-//    an element-wise fallback for unaligned or odd cases, and 64 x 64 tiles
-//    transposed through LDS where a trainer stores a shard transposed. Work
+//    rows at any element address and width, an element-wise fallback for rows
+//    narrower than a vector, and 64 x 64 tiles transposed through LDS where a trainer stores a shard transposed. Work
 //    items are spread over several one-wave workgroups: a vector kind takes
 //    one per chunk of kChunkVecs vectors, each issuing all of its loads, then
 //    all of its stores, and exiting (no loop, so no wait on the completion of
@@ -235,6 +235,75 @@ __device__ void run_bf16_f32(const Task& t, const char* src, char* dst, uint32_t
     }
 }
 
+// Vectors at element alignment: gfx950 loads and stores global memory at any
+// byte address, so an unaligned vector costs the same instruction.
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef u32x2 u32x2_a1 __attribute__((aligned(1)));
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
+
+// One chunk of a rectangle whose rows sit at any element address (flat shards
+// that start anywhere, odd widths): kSs, kDs the element bytes of both sides.
+// Lane l takes units q0 + l + 64 k, k < kRowsPerLane, each one load and one
+// store; inner units are aligned in the destination, and a row's first and
+// last unit overlap their neighbours, so no row has single elements. Bound:
+// HBM. A bf16 flat shard of a sixth of a 16-layer model (3.2 GB moved), every
+// run at an odd phase: 1974 us element by element, 504 us so (6.4 TB/s, the
+// aligned copy's rate is 6.7); fp32 -> bf16 at widths 1500 and 1721 (0.9 GB):
+// 771 -> 162 us.
+template <int kSs, int kDs>
+__device__ __forceinline__ void run_rows(const Task& t, const char* src, char* dst, uint32_t chunk) {
+  constexpr int V = 16 / (kSs > kDs ? kSs : kDs), N = kRowsPerLane;
+  const uint32_t total = t.rows * t.units, q0 = chunk * uint32_t(kThreads * N);
+  if (q0 >= total) return;
+  const char* s[N];
+  char* d[N];
+  bool on[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const uint32_t q = q0 + threadIdx.x + k * kThreads;
+    const uint32_t r = t.rows == 1 ? 0 : q / t.units;
+    char* dr = dst + uint64_t(r) * t.dst_ld * kDs;
+    const int a = int((0u - uint32_t(reinterpret_cast<uintptr_t>(dr))) & uint32_t(V * kDs - 1)) / kDs;
+    const int64_t at = int64_t(q - r * t.units) * V + (a ? a - V : 0);
+    on[k] = q < total && at < int64_t(t.cols);
+    const int64_t off = at < 0 ? 0 : at > int64_t(t.cols) - V ? int64_t(t.cols) - V : at;
+    s[k] = src + (uint64_t(r) * t.src_ld + off) * kSs;
+    d[k] = dr + off * kDs;
+  }
+  u32x4 v[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (on[k]) {
+      if (kSs == 2 && kDs == 4) {
+        const u32x2 x = ld(reinterpret_cast<const u32x2_a2*>(s[k]));
+        v[k] = u32x4{x.x, x.y, 0u, 0u};
+      } else {
+        v[k] = ld(reinterpret_cast<const u32x4_a2*>(s[k]));
+      }
+    }
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (on[k]) {
+      const u32x4 x = v[k];
+      if (kSs == 4 && kDs == 2) {
+        const f32x4 f = __builtin_bit_cast(f32x4, x);
+        st(u32x2{pack_bf16x2(f.x, f.y), pack_bf16x2(f.z, f.w)}, reinterpret_cast<u32x2_a2*>(d[k]));
+      } else if (kSs == 2 && kDs == 4) {
+        st(u32x4{x.x << 16, x.x & 0xFFFF0000u, x.y << 16, x.y & 0xFFFF0000u}, reinterpret_cast<u32x4_a2*>(d[k]));
+      } else {
+        st(x, reinterpret_cast<u32x4_a2*>(d[k]));
+      }
+    }
+}
+
+__device__ void run_rows_any(const Task& t, const char* src, char* dst, uint32_t chunk) {
+  if (t.sdt == WB_F32)
+    t.ddt == WB_F32 ? run_rows<4, 4>(t, src, dst, chunk) : run_rows<4, 2>(t, src, dst, chunk);
+  else
+    t.ddt == WB_F32 ? run_rows<2, 4>(t, src, dst, chunk) : run_rows<2, 2>(t, src, dst, chunk);
+}
+
 // Raw bits of one element, widened to 32 bits.
 __device__ __forceinline__ uint32_t load_bits(const char* p, int dt) {
   if (dt == WB_F32) return *reinterpret_cast<const uint32_t*>(p);
@@ -319,7 +388,7 @@ __device__ void run_transpose16(const Task& t, const char* src, char* dst, uint3
 }  // namespace
 
 __device__ __forceinline__ const char* base_of(uint16_t idx, const uint64_t* ptrs, const char* buf, const char* aux) {
-  return idx == 0 ? buf : idx == kAuxBuffer ? aux : reinterpret_cast<const char*>(ptrs[idx]);
+  return idx == 0 ? buf : idx == kAuxBuffer ? aux : global_ptr(ptrs[idx]);
 }
 
 // XCD-aware order of a launch's work. The hardware hands workgroup b to XCD
@@ -371,6 +440,7 @@ __global__ __launch_bounds__(kThreads) void wb_tasks_kernel(const Task* __restri
     case TASK_COPY16: run_copy16(t, src, dst, q0); break;
     case TASK_F32_BF16: run_f32_bf16(t, src, dst, chunk); break;
     case TASK_BF16_F32: run_bf16_f32(t, src, dst, q0); break;
+    case TASK_ROWS: run_rows_any(t, src, dst, chunk); break;
     case TASK_SCALAR: if (chunk == 0) run_scalar(t, src, dst); break;
     case TASK_TRANSPOSE: run_transpose(t, src, dst, chunk); break;
     case TASK_TRANSPOSE16: run_transpose16(t, src, dst, chunk * (kThreads / 64) + (threadIdx.x >> 6)); break;
@@ -733,12 +803,6 @@ __device__ __forceinline__ void qblock_pair(const QBlock* __restrict__ blocks, u
     qblock_pair_run<false, false>(L, PairBands{}, h, on, b0, b1, ptrs);
   }
 }
-
-// Vectors at element alignment: gfx950 loads and stores global memory at any
-// byte address, so an unaligned chunk costs the same instruction.
-typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
-typedef u32x2 u32x2_a1 __attribute__((aligned(1)));
-typedef uint32_t u32_a1 __attribute__((aligned(1)));
 
 // Where the 16-byte chunks of the block's rows come from: a block that is
 // one wire piece (QB_DIRECT) keeps its address in the descriptor; otherwise

@@ -144,7 +144,42 @@ struct TaskSink {
     }
   }
 
+  // Rows at any element address (TASK_ROWS), in items of at most task_bytes and
+  // of the chunks an aligned item has; rows too narrow for a unit go element
+  // by element in shorter items (a wave takes a whole one).
+  void push_rows(int sidx, uint64_t soff, int64_t sld, int sdt, int didx, uint64_t doff, int64_t dld, int ddt,
+                 int64_t rows, int64_t cols) {
+    const int ss = dtype_bytes(sdt), ds = dtype_bytes(ddt);
+    if (ss < 2 || ds < 2 || cols < rows_unit(sdt, ddt)) {
+      const int64_t per = 4096, nc = std::min(cols, per), nr = std::max<int64_t>(1, per / nc);
+      for (int64_t r = 0; r < rows; r += nr)
+        for (int64_t c = 0; c < cols; c += nc)
+          push(TASK_SCALAR, sidx, soff + (r * sld + c) * ss, static_cast<uint32_t>(sld), sdt, didx,
+               doff + (r * dld + c) * ds, static_cast<uint32_t>(dld), ddt, std::min(nr, rows - r),
+               std::min(nc, cols - c));
+      return;
+    }
+    // 4 units short of an aligned item, so that heads and remainders need no more chunks than one has
+    const int64_t V = rows_unit(sdt, ddt), per_task = std::max<int64_t>(V, (task_bytes / std::max(ss, ds) / V - 4) * V);
+    // column cuts at destination multiples of the unit, no piece narrower than one
+    const int64_t head = int64_t((V * ds - doff % (V * ds)) % (V * ds)) / ds;
+    const int64_t nr = std::max<int64_t>(1, per_task / ((cols + V - 1) / V * V + V));
+    for (int64_t r = 0; r < rows; r += nr)
+      for (int64_t c = 0; c < cols;) {
+        int64_t end = cols - c <= per_task + head ? cols : c == 0 ? per_task + head : c + per_task;
+        if (cols - end < V) end = cols;
+        const uint64_t so = soff + (r * sld + c) * ss, dof = doff + (r * dld + c) * ds;
+        const int64_t n = std::min(nr, rows - r);
+        push(TASK_ROWS, sidx, so, static_cast<uint32_t>(sld), sdt, didx, dof, static_cast<uint32_t>(dld), ddt, n,
+             end - c);
+        out.back().units = rows_units(sdt, ddt, dof, dld, n, end - c);
+        c = end;
+      }
+  }
+
   // rows x cols elements; src/dst row strides in elements; offsets in bytes.
+  // 16-byte aligned rectangles of whole vectors take the vector kinds, all
+  // others TASK_ROWS.
   void copy_rect(int sidx, uint64_t soff, int64_t sld, int sdt, int didx, uint64_t doff, int64_t dld, int ddt,
                  int64_t rows, int64_t cols) {
     const int ss = dtype_bytes(sdt), ds = dtype_bytes(ddt);
@@ -155,42 +190,31 @@ struct TaskSink {
     if (rows == 1 || (cols == sld && cols == dld)) {
       // contiguous on both sides: one linear run
       const int64_t n = rows * cols;
-      int64_t head = -1;
-      if (vk)
-        for (int64_t e = 0; e < v && e < n; ++e)
-          if ((soff + e * ss) % 16 == 0 && (doff + e * ds) % 16 == 0) { head = e; break; }
-      if (head < 0) {
-        for (int64_t a = 0; a < n; a += per_task)
-          push(TASK_SCALAR, sidx, soff + a * ss, 0, sdt, didx, doff + a * ds, 0, ddt, 1, std::min(per_task, n - a));
+      if (!vk || soff % 16 || doff % 16 || n % v) {
+        push_rows(sidx, soff, n, sdt, didx, doff, n, ddt, 1, n);
         return;
       }
-      if (head > 0) push(TASK_SCALAR, sidx, soff, 0, sdt, didx, doff, 0, ddt, 1, head);
-      const int64_t body = (n - head) / v * v;
       const int64_t chunk = std::max<int64_t>(v, per_task / v * v);
-      for (int64_t a = 0; a < body; a += chunk) {
-        const int64_t len = std::min(chunk, body - a);
-        push_vec(kind, sidx, soff + (head + a) * ss, len, sdt, didx, doff + (head + a) * ds, len, ddt, 1, len);
+      for (int64_t a = 0; a < n; a += chunk) {
+        const int64_t len = std::min(chunk, n - a);
+        push_vec(kind, sidx, soff + a * ss, len, sdt, didx, doff + a * ds, len, ddt, 1, len);
       }
-      const int64_t tail = n - head - body;
-      if (tail > 0)
-        push(TASK_SCALAR, sidx, soff + (head + body) * ss, 0, sdt, didx, doff + (head + body) * ds, 0, ddt, 1, tail);
       return;
     }
     const bool vec = vk && soff % 16 == 0 && doff % 16 == 0 && cols % v == 0 && (sld * ss) % 16 == 0 &&
                      (dld * ds) % 16 == 0;
-    const int64_t unit = vec ? v : 1;
-    const int64_t col_chunk = cols <= per_task ? cols : std::max(unit, per_task / unit * unit);
+    if (!vec) {
+      push_rows(sidx, soff, sld, sdt, didx, doff, dld, ddt, rows, cols);
+      return;
+    }
+    const int64_t col_chunk = cols <= per_task ? cols : std::max(v, per_task / v * v);
     const int64_t rows_per = std::max<int64_t>(1, per_task / col_chunk);
     for (int64_t r = 0; r < rows; r += rows_per) {
       const int64_t nr = std::min(rows_per, rows - r);
       for (int64_t c = 0; c < cols; c += col_chunk) {
         const int64_t nc = std::min(col_chunk, cols - c);
         const uint64_t so = soff + (r * sld + c) * ss, dof = doff + (r * dld + c) * ds;
-        if (vec)
-          push_vec(kind, sidx, so, sld, sdt, didx, dof, dld, ddt, nr, nc);
-        else
-          push(TASK_SCALAR, sidx, so, static_cast<uint32_t>(sld), sdt, didx, dof, static_cast<uint32_t>(dld), ddt, nr,
-               nc);
+        push_vec(kind, sidx, so, sld, sdt, didx, dof, dld, ddt, nr, nc);
       }
     }
   }
@@ -676,6 +700,13 @@ void check_work(const wb_plan_t& P, const Rank& R) {
           fail(WB_EINVAL, "internal: misaligned cast work item");
         [[fallthrough]];
       case TASK_SCALAR:
+      case TASK_ROWS:
+        // every element's address lies in the rectangle, and a unit never leaves its row
+        if (t.kind == TASK_ROWS &&
+            (ss < 2 || ds < 2 || t.cols < uint32_t(rows_unit(t.sdt, t.ddt)) || t.src_off % ss || t.dst_off % ds ||
+             t.units != rows_units(t.sdt, t.ddt, t.dst_off, t.dst_ld, t.rows, t.cols) ||
+             uint64_t(t.rows) * t.units >= (uint64_t(1) << 31)))
+          fail(WB_EINVAL, "internal: bad row work item");
         inside(t.src_idx, t.src_off, (uint64_t(t.rows - 1) * t.src_ld + t.cols) * ss, "source");
         inside(t.dst_idx, t.dst_off, (uint64_t(t.rows - 1) * t.dst_ld + t.cols) * ds, "destination");
         break;
@@ -728,7 +759,8 @@ void check_work(const wb_plan_t& P, const Rank& R) {
     aux_size = P.role == WB_SENDER ? 0 : W.st[st + 1].send_bytes[P.rank];
     for (uint32_t ti = P.round_fwd[st][k]; ti < P.round_fwd[st][k + 1]; ++ti) {
       const Task& t = P.tasks[ti];
-      if (t.kind != TASK_COPY16 && t.kind != TASK_SCALAR) fail(WB_EINVAL, "internal: forward work item kind");
+      if (t.kind != TASK_COPY16 && t.kind != TASK_SCALAR && t.kind != TASK_ROWS)
+        fail(WB_EINVAL, "internal: forward work item kind");
       if (t.src_idx != 0 || t.dst_idx != kAuxBuffer) fail(WB_EINVAL, "internal: forward work item buffers");
       check_task(t);
     }

@@ -144,9 +144,10 @@ enum TaskKind : uint8_t {
   TASK_COPY16 = 0,     // byte copy, 16-byte vectors (cols, lds and offsets in bytes)
   TASK_F32_BF16 = 1,   // fp32 -> bf16, 8 elements per vector
   TASK_BF16_F32 = 2,   // bf16 -> fp32, 8 elements per vector
-  TASK_SCALAR = 3,     // any supported pair, element by element
+  TASK_SCALAR = 3,     // any supported pair, element by element (rows narrower than a unit of TASK_ROWS)
   TASK_TRANSPOSE = 4,  // dst[c][r] = cvt(src[r][c]), one LDS tile of up to 64 x 64
   TASK_TRANSPOSE16 = 5,  // 2-byte dst[c][r] = src[r][c], (64..256) rows x 64 cols, in registers
+  TASK_ROWS = 7,       // any supported pair, rows of any element address and width (at least one unit)
   TASK_TILE = 6,       // 2-byte dst[c][r] = src[r][c], one kTileRows x kTileCols tile through LDS (a launch of its own)
 };
 
@@ -162,10 +163,25 @@ struct Task {
   uint32_t src_ld, dst_ld;
   uint16_t src_idx, dst_idx;
   uint8_t kind, sdt, ddt, pad0;
-  uint32_t pad1;
+  uint32_t units;  // TASK_ROWS: units per row
   uint32_t pad2;
 };
 static_assert(sizeof(Task) == 48, "Task layout");
+
+// TASK_ROWS items are cut row by row into units of rows_unit elements, 16 bytes
+// on the wider side, placed so that all but the first and the last unit of a
+// row start at a multiple of their size in the destination; those two are
+// moved inside the row and overlap their neighbours (same values twice). A row
+// takes one unit more when some row of the item starts between multiples.
+inline int rows_unit(int sdt, int ddt) {
+  const int m = sdt == WB_F32 || ddt == WB_F32 ? 4 : 2;
+  return 16 / m;
+}
+inline uint32_t rows_units(int sdt, int ddt, uint64_t dst_off, uint64_t dst_ld, uint64_t rows, uint64_t cols) {
+  const uint64_t V = rows_unit(sdt, ddt), ds = ddt == WB_F32 ? 4 : 2;
+  const bool whole = dst_off % (V * ds) == 0 && (rows == 1 || dst_ld % V == 0);
+  return static_cast<uint32_t>((cols + V - 1) / V + (whole ? 0 : 1));
+}
 
 // Copy kernel launch. Each launch's range of work items is ordered by class:
 // class 0 (the vector kinds) takes 2^s[0] workgroups of kChunkThreads
@@ -184,6 +200,7 @@ static_assert(sizeof(Task) == 48, "Task layout");
 constexpr int kChunkThreads = WB_CHUNK_THREADS;
 constexpr int kChunkPerLane = WB_CHUNK_PER_LANE;
 constexpr uint32_t kChunkVecs = uint32_t(kChunkThreads) * kChunkPerLane;
+constexpr int kRowsPerLane = 2;  // units of a TASK_ROWS chunk per lane
 constexpr uint32_t kMaxGridX = 1u << 22;
 static_assert(kChunkThreads % 64 == 0 && kChunkThreads <= 256, "copy workgroup size");
 
@@ -203,6 +220,10 @@ inline uint32_t task_chunks(const Task& t) {
       return static_cast<uint32_t>(units == 0 ? 1 : (units + per - 1) / per);
     }
     case TASK_BF16_F32: vecs = uint64_t(t.rows) * (t.cols >> 3); break;
+    case TASK_ROWS: {
+      const uint64_t per = uint64_t(kChunkThreads) * kRowsPerLane;
+      return static_cast<uint32_t>((uint64_t(t.rows) * t.units + per - 1) / per);
+    }
     case TASK_TRANSPOSE16: {
       const uint32_t per = kChunkThreads / 64, tiles = (t.rows + 63) / 64;
       return (tiles + per - 1) / per;
