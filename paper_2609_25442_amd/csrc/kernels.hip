@@ -244,57 +244,38 @@ typedef uint32_t u32_a1 __attribute__((aligned(1)));
 
 // One chunk of a rectangle whose rows sit at any element address (flat shards
 // that start anywhere, odd widths): kSs, kDs the element bytes of both sides.
-// Lane l takes units q0 + l + 64 k, k < kRowsPerLane, each one load and one
-// store; inner units are aligned in the destination, and a row's first and
-// last unit overlap their neighbours, so no row has single elements. Bound:
-// HBM. A bf16 flat shard of a sixth of a 16-layer model (3.2 GB moved), every
-// run at an odd phase: 1974 us element by element, 504 us so (6.4 TB/s, the
-// aligned copy's rate is 6.7); fp32 -> bf16 at widths 1500 and 1721 (0.9 GB):
-// 771 -> 162 us.
+// Lane l of chunk c takes unit 64 c + l: one load and one store; inner units
+// are aligned in the destination, and a row's first and last unit overlap
+// their neighbours, so no row has single elements. Bound: HBM. A bf16 flat
+// shard of a sixth of a 16-layer model (3.2 GB moved), every run at an odd
+// phase: 1974 us element by element, 487 us so (6.6 TB/s, the aligned copy's
+// rate is 6.7); fp32 -> bf16 at widths 1500 and 1721 (0.9 GB): 771 -> 157 us.
+// Two units per lane: 503 and 161 us.
 template <int kSs, int kDs>
 __device__ __forceinline__ void run_rows(const Task& t, const char* src, char* dst, uint32_t chunk) {
-  constexpr int V = 16 / (kSs > kDs ? kSs : kDs), N = kRowsPerLane;
-  const uint32_t total = t.rows * t.units, q0 = chunk * uint32_t(kThreads * N);
-  if (q0 >= total) return;
-  const char* s[N];
-  char* d[N];
-  bool on[N];
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const uint32_t q = q0 + threadIdx.x + k * kThreads;
-    const uint32_t r = t.rows == 1 ? 0 : q / t.units;
-    char* dr = dst + uint64_t(r) * t.dst_ld * kDs;
-    const int a = int((0u - uint32_t(reinterpret_cast<uintptr_t>(dr))) & uint32_t(V * kDs - 1)) / kDs;
-    const int64_t at = int64_t(q - r * t.units) * V + (a ? a - V : 0);
-    on[k] = q < total && at < int64_t(t.cols);
-    const int64_t off = at < 0 ? 0 : at > int64_t(t.cols) - V ? int64_t(t.cols) - V : at;
-    s[k] = src + (uint64_t(r) * t.src_ld + off) * kSs;
-    d[k] = dr + off * kDs;
+  constexpr int V = 16 / (kSs > kDs ? kSs : kDs);
+  const uint32_t q = chunk * uint32_t(kThreads) + threadIdx.x;
+  if (q >= t.rows * t.units) return;
+  const uint32_t r = t.rows == 1 ? 0 : q / t.units;
+  char* dr = dst + uint64_t(r) * t.dst_ld * kDs;
+  const int a = int((0u - uint32_t(reinterpret_cast<uintptr_t>(dr))) & uint32_t(V * kDs - 1)) / kDs;
+  const int64_t at = int64_t(q - r * t.units) * V + (a ? a - V : 0);
+  if (at >= int64_t(t.cols)) return;
+  const int64_t off = at < 0 ? 0 : at > int64_t(t.cols) - V ? int64_t(t.cols) - V : at;
+  const char* s = src + (uint64_t(r) * t.src_ld + off) * kSs;
+  char* d = dr + off * kDs;
+  if (kSs == 2 && kDs == 4) {
+    const u32x2 x = ld(reinterpret_cast<const u32x2_a2*>(s));
+    st(u32x4{x.x << 16, x.x & 0xFFFF0000u, x.y << 16, x.y & 0xFFFF0000u}, reinterpret_cast<u32x4_a2*>(d));
+    return;
   }
-  u32x4 v[N];
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-    if (on[k]) {
-      if (kSs == 2 && kDs == 4) {
-        const u32x2 x = ld(reinterpret_cast<const u32x2_a2*>(s[k]));
-        v[k] = u32x4{x.x, x.y, 0u, 0u};
-      } else {
-        v[k] = ld(reinterpret_cast<const u32x4_a2*>(s[k]));
-      }
-    }
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-    if (on[k]) {
-      const u32x4 x = v[k];
-      if (kSs == 4 && kDs == 2) {
-        const f32x4 f = __builtin_bit_cast(f32x4, x);
-        st(u32x2{pack_bf16x2(f.x, f.y), pack_bf16x2(f.z, f.w)}, reinterpret_cast<u32x2_a2*>(d[k]));
-      } else if (kSs == 2 && kDs == 4) {
-        st(u32x4{x.x << 16, x.x & 0xFFFF0000u, x.y << 16, x.y & 0xFFFF0000u}, reinterpret_cast<u32x4_a2*>(d[k]));
-      } else {
-        st(x, reinterpret_cast<u32x4_a2*>(d[k]));
-      }
-    }
+  const u32x4 x = ld(reinterpret_cast<const u32x4_a2*>(s));
+  if (kSs == 4 && kDs == 2) {
+    const f32x4 f = __builtin_bit_cast(f32x4, x);
+    st(u32x2{pack_bf16x2(f.x, f.y), pack_bf16x2(f.z, f.w)}, reinterpret_cast<u32x2_a2*>(d));
+  } else {
+    st(x, reinterpret_cast<u32x4_a2*>(d));
+  }
 }
 
 __device__ void run_rows_any(const Task& t, const char* src, char* dst, uint32_t chunk) {

@@ -159,8 +159,10 @@ struct TaskSink {
                std::min(nc, cols - c));
       return;
     }
-    // 4 units short of an aligned item, so that heads and remainders need no more chunks than one has
-    const int64_t V = rows_unit(sdt, ddt), per_task = std::max<int64_t>(V, (task_bytes / std::max(ss, ds) / V - 4) * V);
+    // 4 units short of the chunks of an aligned item (a cast's are two units a
+    // lane wide), so that heads and remainders need no more of them than it has
+    const int64_t V = rows_unit(sdt, ddt), aligned = task_bytes / std::max(ss, ds) / V;
+    const int64_t per_task = std::max<int64_t>(V, ((sdt == ddt ? aligned : aligned / 2) - 4) * V);
     // column cuts at destination multiples of the unit, no piece narrower than one
     const int64_t head = int64_t((V * ds - doff % (V * ds)) % (V * ds)) / ds;
     const int64_t nr = std::max<int64_t>(1, per_task / ((cols + V - 1) / V * V + V));

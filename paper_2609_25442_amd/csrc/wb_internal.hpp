@@ -200,7 +200,6 @@ inline uint32_t rows_units(int sdt, int ddt, uint64_t dst_off, uint64_t dst_ld, 
 constexpr int kChunkThreads = WB_CHUNK_THREADS;
 constexpr int kChunkPerLane = WB_CHUNK_PER_LANE;
 constexpr uint32_t kChunkVecs = uint32_t(kChunkThreads) * kChunkPerLane;
-constexpr int kRowsPerLane = 2;  // units of a TASK_ROWS chunk per lane
 constexpr uint32_t kMaxGridX = 1u << 22;
 static_assert(kChunkThreads % 64 == 0 && kChunkThreads <= 256, "copy workgroup size");
 
@@ -221,8 +220,8 @@ inline uint32_t task_chunks(const Task& t) {
     }
     case TASK_BF16_F32: vecs = uint64_t(t.rows) * (t.cols >> 3); break;
     case TASK_ROWS: {
-      const uint64_t per = uint64_t(kChunkThreads) * kRowsPerLane;
-      return static_cast<uint32_t>((uint64_t(t.rows) * t.units + per - 1) / per);
+      const uint64_t units = uint64_t(t.rows) * t.units;  // one per lane
+      return static_cast<uint32_t>((units + kChunkThreads - 1) / kChunkThreads);
     }
     case TASK_TRANSPOSE16: {
       const uint32_t per = kChunkThreads / 64, tiles = (t.rows + 63) / 64;
