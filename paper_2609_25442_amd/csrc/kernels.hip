@@ -45,13 +45,13 @@ namespace {
 #ifndef WB_TASK_DYN_LDS
 #define WB_TASK_DYN_LDS 0
 #endif
-// The fp8 block kernel reserves enough dynamic LDS to hold two workgroups per
-// CU (two waves per SIMD): more resident workgroups, each gathering 128 rows
-// at once, were slower (measured) and the cap leaves the kernel the registers
-// of every block class without costing occupancy.
-#ifndef WB_QBLOCK_DYN_LDS
-#define WB_QBLOCK_DYN_LDS 65536
-#endif
+// The fp8 block kernel reserves dynamic LDS to cap the workgroups per CU: two
+// (64 KiB) where most blocks go in pairs, three (48 KiB) where most go one per
+// workgroup. Three against two for pairs: 1.5 % slower on 2048 and 4096
+// column rows (0.45 and 0.53 ms launches), 0.5 % faster on 7168; for single
+// fp32 blocks 5.5 % faster (whole unpack 2.06 -> 1.95 ms); four are not to be
+// had with this kernel's registers.
+constexpr unsigned kQBlockLdsPairs = 65536, kQBlockLdsSingles = 49152;
 
 constexpr int kThreads = kChunkThreads;
 
@@ -828,7 +828,7 @@ struct BlockSource {
 // V is moved left over its neighbour (the same values, written twice).
 // Bound: HBM; 8 (16) 16-byte loads per thread are in flight at once. An fp32
 // rank of half an 8 B dense model (7.0 GB of blocks in, 1.7 GB out): 8.22 ms when
-// every element searched its piece, 1.56 ms now (5.6 TB/s). For bf16, chunks of
+// every element searched its piece, 1.46 ms now (6.0 TB/s). For bf16, chunks of
 // 4 elements on 32 threads a row made blocks of 32 row bands 6 % slower than
 // 8 on 16: twice the row lookups.
 template <bool kF32, int kKind>
@@ -1086,8 +1086,8 @@ int launch_qblocks(const QBlock* blocks, uint32_t n, uint32_t nfull, uint32_t np
                    const uint64_t* ptrs, const void* buf, void* stream) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(wb_qblock_kernel, dim3(qblock_workgroups(n, nfull, npair)), dim3(kQBlockThreads),
-                     WB_QBLOCK_DYN_LDS, static_cast<hipStream_t>(stream), blocks, pieces, ptrs,
-                     static_cast<const char*>(buf), n, nfull, npair);
+                     n - npair > npair ? kQBlockLdsSingles : kQBlockLdsPairs, static_cast<hipStream_t>(stream), blocks,
+                     pieces, ptrs, static_cast<const char*>(buf), n, nfull, npair);
   return hipGetLastError();
 }
 
