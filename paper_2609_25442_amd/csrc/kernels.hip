@@ -352,8 +352,8 @@ __device__ __forceinline__ u32x4 column8(const u32x4 (&a)[8], int j) {
 // dst[c][r] = src[r][c] for 2-byte elements, (64..256) rows x 64 columns: each
 // wave takes one 64 x 64 tile (tile `w` of the item, counted down the rows),
 // each lane an 8 x 8 sub-tile that it loads as eight 16-byte rows, transposes
-// in registers and stores as eight 16-byte rows. Lanes 8i..8i+7 cover one
-// 128-byte span of a row on both sides.
+// in registers and stores as eight 16-byte rows, at any element address on
+// both sides. Lanes 8i..8i+7 cover one 128-byte span of a row on both sides.
 __device__ void run_transpose16(const Task& t, const char* src, char* dst, uint32_t w) {
   const uint32_t l = threadIdx.x & 63;
   if (w * 64 >= t.rows) return;
@@ -361,9 +361,49 @@ __device__ void run_transpose16(const Task& t, const char* src, char* dst, uint3
   u32x4 a[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
-    a[i] = ld(reinterpret_cast<const u32x4*>(src + (uint64_t(r0 + i) * t.src_ld + c0) * 2));
+    a[i] = ld(reinterpret_cast<const u32x4_a2*>(src + (uint64_t(r0 + i) * t.src_ld + c0) * 2));
 #pragma unroll
-  for (int j = 0; j < 8; ++j) st(column8(a, j), reinterpret_cast<u32x4*>(dst + (uint64_t(c0 + j) * t.dst_ld + r0) * 2));
+  for (int j = 0; j < 8; ++j)
+    st(column8(a, j), reinterpret_cast<u32x4_a2*>(dst + (uint64_t(c0 + j) * t.dst_ld + r0) * 2));
+}
+
+// dst[c][r] = cvt(src[r][c]) with fp32 on at least one side, (32..128) rows x
+// 32 columns: the same with 4 x 4 sub-tiles and 32 x 32 tiles, a 16-byte row
+// of a sub-tile on each fp32 side and an 8-byte one on a bf16 side.
+template <int kSs, int kDs>
+__device__ __forceinline__ void run_transpose4(const Task& t, const char* src, char* dst, uint32_t w) {
+  const uint32_t l = threadIdx.x & 63;
+  if (w * 32 >= t.rows) return;
+  const uint32_t c0 = 4 * (l & 7), r0 = w * 32 + 4 * (l >> 3);
+  u32x4 a[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const char* p = src + (uint64_t(r0 + i) * t.src_ld + c0) * kSs;
+    if (kSs == 4) {
+      a[i] = ld(reinterpret_cast<const u32x4_a2*>(p));
+    } else {
+      const u32x2 x = ld(reinterpret_cast<const u32x2_a2*>(p));
+      a[i] = u32x4{x.x << 16, x.x & 0xFFFF0000u, x.y << 16, x.y & 0xFFFF0000u};
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    char* p = dst + (uint64_t(c0 + j) * t.dst_ld + r0) * kDs;
+    if (kDs == 4) {
+      st(u32x4{a[0][j], a[1][j], a[2][j], a[3][j]}, reinterpret_cast<u32x4_a2*>(p));
+    } else {
+      st(u32x2{pack_bf16x2(__uint_as_float(a[0][j]), __uint_as_float(a[1][j])),
+               pack_bf16x2(__uint_as_float(a[2][j]), __uint_as_float(a[3][j]))},
+         reinterpret_cast<u32x2_a2*>(p));
+    }
+  }
+}
+
+__device__ void run_transpose4_any(const Task& t, const char* src, char* dst, uint32_t w) {
+  if (t.sdt == WB_F32)
+    t.ddt == WB_F32 ? run_transpose4<4, 4>(t, src, dst, w) : run_transpose4<4, 2>(t, src, dst, w);
+  else
+    run_transpose4<2, 4>(t, src, dst, w);
 }
 
 }  // namespace
@@ -425,44 +465,62 @@ __global__ __launch_bounds__(kThreads) void wb_tasks_kernel(const Task* __restri
     case TASK_SCALAR: if (chunk == 0) run_scalar(t, src, dst); break;
     case TASK_TRANSPOSE: run_transpose(t, src, dst, chunk); break;
     case TASK_TRANSPOSE16: run_transpose16(t, src, dst, chunk * (kThreads / 64) + (threadIdx.x >> 6)); break;
+    case TASK_TRANSPOSE4: run_transpose4_any(t, src, dst, chunk * (kThreads / 64) + (threadIdx.x >> 6)); break;
     default: break;
   }
 }
 
-// dst[c][r] = src[r][c] of one kTileRows x kTileCols tile of 2-byte elements
-// per workgroup (TASK_TILE items): thread t transposes the 8 x 8 sub-tile at
-// source rows 8 (t / 64) .., columns 8 (t mod 64) .. in registers (a wave
-// instruction reads 1 KiB of one source row), LDS regroups the sub-tiles by
-// destination row, and each thread then stores eight 16-byte pieces of
-// destination rows (a wave instruction writes four whole 256-byte rows). The
-// 16-byte words of destination row r sit in LDS at word w ^ ((r / 8) mod 16):
-// the sub-tiles of one wave land in 16 different bank groups, and a row read
-// back is a permutation of its own words.
-__global__ __launch_bounds__(kTileThreads) void wb_tile_kernel(const Task* __restrict__ tasks,
-                                                               const uint64_t* __restrict__ ptrs, const char* buf,
-                                                               const char* aux) {
-  constexpr int GR = kTileRows / 8, GC = kTileCols / 8;  // 16-byte words per destination / source row
-  __shared__ u32x4 lds[kTileCols][GR];
-  const Task t = tasks[blockIdx.x];
-  const char* src = base_of(t.src_idx, ptrs, buf, aux) + t.src_off;
-  char* dst = const_cast<char*>(base_of(t.dst_idx, ptrs, buf, aux)) + t.dst_off;
+// dst[c][r] = src[r][c] of one tile per workgroup (TASK_TILE items): kTileRows x
+// kTileCols 2-byte elements, or kTileRows x kTileCols / 2 4-byte ones. Thread t
+// takes the 16-byte words at source rows 8 (t / 64) .. + 7, word t mod 64 (a
+// wave instruction reads 1 KiB of one source row), and transposes them in
+// registers: an 8 x 8 sub-tile of 2-byte elements, two 4 x 4 ones of 4-byte.
+// LDS regroups the sub-tiles by destination row, and each thread then stores
+// eight 16-byte pieces of destination rows (a wave instruction writes four
+// whole 256-byte rows, or two of 512 bytes). Word w of destination row r sits
+// in LDS at w ^ ((r / 8) mod 16), or w ^ ((r / 4) mod 32): the sub-tiles of one
+// wave land in different banks, and a row read back is a permutation of its
+// own words. Bound: HBM, one workgroup (16 waves) per CU by its LDS. 4-byte
+// tiles took the fp32 pack of a TP4 rank of half an 8 B dense model (2.4 of
+// its 9.1 GB transposed) from 1.64 (LDS tiles of 32 x 32) to 1.42 ms (6.4 TB/s).
+template <int kEs>
+__device__ __forceinline__ void run_tile(const Task& t, const char* src, char* dst, u32x4* lds) {
+  constexpr int V = 16 / kEs, GC = kTileCols * 2 / 16;  // elements per word, words per source row
+  constexpr int GR = kTileRows / V, H = 8 / V;          // words per destination row, words a thread gives each
   const int cg = threadIdx.x % GC, rg = threadIdx.x / GC;
   u32x4 a[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
-    a[i] = ld(reinterpret_cast<const u32x4*>(src + (uint64_t(8 * rg + i) * t.src_ld + 8 * cg) * 2));
+    a[i] = ld(reinterpret_cast<const u32x4*>(src + (uint64_t(8 * rg + i) * t.src_ld + V * cg) * kEs));
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int row = 8 * cg + j;  // destination row
-    lds[row][rg ^ ((row >> 3) & (GR - 1))] = column8(a, j);
+  for (int j = 0; j < V; ++j) {
+    u32x4* row = lds + (V * cg + j) * GR;  // destination row V cg + j
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+      row[(rg * H + h) ^ (cg & (GR - 1))] =
+          kEs == 2 ? column8(a, j) : u32x4{a[(4 * h) & 7][j & 3], a[(4 * h + 1) & 7][j & 3], a[(4 * h + 2) & 7][j & 3], a[(4 * h + 3) & 7][j & 3]};
   }
   __syncthreads();
   const int w = threadIdx.x % GR, r0 = threadIdx.x / GR;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const int row = r0 + (kTileThreads / GR) * k;
-    st(lds[row][w ^ ((row >> 3) & (GR - 1))], reinterpret_cast<u32x4*>(dst + (uint64_t(row) * t.dst_ld + 8 * w) * 2));
+    st(lds[row * GR + (w ^ ((row / V) & (GR - 1)))],
+       reinterpret_cast<u32x4*>(dst + (uint64_t(row) * t.dst_ld + V * w) * kEs));
   }
+}
+
+__global__ __launch_bounds__(kTileThreads) void wb_tile_kernel(const Task* __restrict__ tasks,
+                                                               const uint64_t* __restrict__ ptrs, const char* buf,
+                                                               const char* aux) {
+  __shared__ u32x4 lds[kTileRows * kTileCols / 8];
+  const Task t = tasks[blockIdx.x];
+  const char* src = base_of(t.src_idx, ptrs, buf, aux) + t.src_off;
+  char* dst = const_cast<char*>(base_of(t.dst_idx, ptrs, buf, aux)) + t.dst_off;
+  if (t.sdt == WB_F32)
+    run_tile<4>(t, src, dst, lds);
+  else
+    run_tile<2>(t, src, dst, lds);
 }
 
 // ---- fp8 E4M3FN blocks ---------------------------------------------------

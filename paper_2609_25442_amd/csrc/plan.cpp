@@ -221,49 +221,62 @@ struct TaskSink {
     }
   }
 
-  // dst[c][r] = src[r][c] for an R x C source block. Aligned 2-byte data is
-  // cut into tiles of 128 source rows by 512 source columns (taken along the
-  // source rows, which measured fastest for these tiles), transposed by the
-  // tile kernel; the edges go to transpose_small.
+  // dst[c][r] = src[r][c] for an R x C source block. Aligned data of one type
+  // is cut into tiles of 128 source rows by 512 (2-byte) or 256 (4-byte) source
+  // columns (taken along the source rows, which measured fastest for these
+  // tiles), transposed by the tile kernel; the edges go to transpose_small.
   void transpose_rect(int sidx, uint64_t soff, int64_t sld, int sdt, int didx, uint64_t doff, int64_t dld, int ddt,
                       int64_t R, int64_t C) {
-    const int ss = dtype_bytes(sdt), ds = dtype_bytes(ddt);
-    const bool fast = ss == 2 && ds == 2 && sdt == ddt && soff % 16 == 0 && doff % 16 == 0 && (sld * 2) % 16 == 0 &&
-                      (dld * 2) % 16 == 0;
-    const int64_t RT = fast ? R / kTileRows * kTileRows : 0, CT = fast ? C / kTileCols * kTileCols : 0;
+    const int es = dtype_bytes(sdt);
+    const bool fast = es >= 2 && sdt == ddt && soff % 16 == 0 && doff % 16 == 0 && (sld * es) % 16 == 0 &&
+                      (dld * es) % 16 == 0;
+    const int64_t TC = fast ? tile_cols(es) : 1;
+    const int64_t RT = fast ? R / kTileRows * kTileRows : 0, CT = fast ? C / TC * TC : 0;
     if (RT == 0 || CT == 0) {
       transpose_small(sidx, soff, sld, sdt, didx, doff, dld, ddt, R, C);
       return;
     }
     for (int64_t r = 0; r < RT; r += kTileRows)
-      for (int64_t c = 0; c < CT; c += kTileCols)
-        push(TASK_TILE, sidx, soff + (r * sld + c) * 2, static_cast<uint32_t>(sld), sdt, didx,
-             doff + (c * dld + r) * 2, static_cast<uint32_t>(dld), ddt, kTileRows, kTileCols);
+      for (int64_t c = 0; c < CT; c += TC)
+        push(TASK_TILE, sidx, soff + (r * sld + c) * es, static_cast<uint32_t>(sld), sdt, didx,
+             doff + (c * dld + r) * es, static_cast<uint32_t>(dld), ddt, kTileRows, TC);
     if (CT < C)  // right strip of the tiled rows
-      transpose_small(sidx, soff + CT * 2, sld, sdt, didx, doff + CT * dld * 2, dld, ddt, RT, C - CT);
+      transpose_small(sidx, soff + CT * es, sld, sdt, didx, doff + CT * dld * es, dld, ddt, RT, C - CT);
     if (RT < R)  // bottom strip, full width
-      transpose_small(sidx, soff + RT * sld * 2, sld, sdt, didx, doff + RT * 2, dld, ddt, R - RT, C);
+      transpose_small(sidx, soff + RT * sld * es, sld, sdt, didx, doff + RT * es, dld, ddt, R - RT, C);
   }
 
-  // The same for blocks without whole tiles. Aligned 2-byte data is
-  // transposed in registers, in items of up to 256 x 64 taken one 64-column
-  // strip at a time, each strip top to bottom: consecutive tiles (and
-  // workgroups) read down the source columns and write neighbouring 128-byte
-  // spans of the same destination rows, an order that measured 9-13 % faster
-  // on gfx950 than row by row. The rest (ragged edges, other dtypes) goes in
-  // 64 x 64 LDS tiles.
+  // The same for blocks without whole tiles: transposed in registers, at any
+  // element address, in items of up to 4 tiles of 64 x 64 (2-byte on both
+  // sides) or 32 x 32 (fp32 on a side), taken one strip of columns at a time,
+  // each strip top to bottom: consecutive tiles (and workgroups) read down the
+  // source columns and write neighbouring spans of the same destination rows,
+  // an order that measured 9-13 % faster on gfx950 than row by row. The last
+  // tiles of a ragged strip are moved back over their neighbours (the same
+  // values, written twice). Blocks smaller than a tile go in 64 x 64 LDS tiles.
   void transpose_small(int sidx, uint64_t soff, int64_t sld, int sdt, int didx, uint64_t doff, int64_t dld, int ddt,
                        int64_t R, int64_t C) {
     const int ss = dtype_bytes(sdt), ds = dtype_bytes(ddt);
-    const bool fast = ss == 2 && ds == 2 && sdt == ddt && soff % 16 == 0 && doff % 16 == 0 && (sld * 2) % 16 == 0 &&
-                      (dld * 2) % 16 == 0;
-    const int64_t R64 = fast ? R / 64 * 64 : 0, C64 = fast ? C / 64 * 64 : 0;
-    for (int64_t c = 0; c < C64; c += 64)
-      for (int64_t r = 0; r < R64; r += 256)
-        push(TASK_TRANSPOSE16, sidx, soff + (r * sld + c) * 2, static_cast<uint32_t>(sld), sdt, didx,
-             doff + (c * dld + r) * 2, static_cast<uint32_t>(dld), ddt, std::min<int64_t>(256, R64 - r), 64);
+    const int64_t E = ss == 2 && ds == 2 ? 64 : 32;
+    if (ss >= 2 && ds >= 2 && R >= E && C >= E) {
+      const uint8_t kind = E == 64 ? TASK_TRANSPOSE16 : TASK_TRANSPOSE4;
+      for (int64_t c0 = 0; c0 < C; c0 += E) {
+        const int64_t c = std::min(c0, C - E);
+        for (int64_t r0 = 0; r0 < R; r0 += 4 * E) {
+          // whole tiles of the item, then one moved back over them
+          const int64_t n = std::min(4 * E, R - r0), whole = n / E * E;
+          const auto item = [&](int64_t r, int64_t rows) {
+            push(kind, sidx, soff + (r * sld + c) * ss, static_cast<uint32_t>(sld), sdt, didx,
+                 doff + (c * dld + r) * ds, static_cast<uint32_t>(dld), ddt, rows, E);
+          };
+          if (whole) item(r0, whole);
+          if (whole < n) item(R - E, E);
+        }
+      }
+      return;
+    }
     for (int64_t r = 0; r < R; r += 64)
-      for (int64_t c = r < R64 ? C64 : 0; c < C; c += 64)
+      for (int64_t c = 0; c < C; c += 64)
         push(TASK_TRANSPOSE, sidx, soff + (r * sld + c) * ss, static_cast<uint32_t>(sld), sdt, didx,
              doff + (c * dld + r) * ds, static_cast<uint32_t>(dld), ddt, std::min<int64_t>(64, R - r),
              std::min<int64_t>(64, C - c));
@@ -718,19 +731,22 @@ void check_work(const wb_plan_t& P, const Rank& R) {
         inside(t.dst_idx, t.dst_off, (uint64_t(t.cols - 1) * t.dst_ld + t.rows) * ds, "transpose destination");
         break;
       case TASK_TILE:
-        if (t.rows != kTileRows || t.cols != kTileCols || ss != 2 || ds != 2 || t.src_off % 16 || t.dst_off % 16 ||
-            (t.src_ld * 2) % 16 || (t.dst_ld * 2) % 16)
+        if (t.rows != kTileRows || ss < 2 || t.sdt != t.ddt || t.cols != uint32_t(tile_cols(int(ss))) ||
+            t.src_off % 16 || t.dst_off % 16 || (t.src_ld * ss) % 16 || (t.dst_ld * ds) % 16)
           fail(WB_EINVAL, "internal: bad transpose tile");
         inside(t.src_idx, t.src_off, (uint64_t(t.rows - 1) * t.src_ld + t.cols) * ss, "transpose source");
         inside(t.dst_idx, t.dst_off, (uint64_t(t.cols - 1) * t.dst_ld + t.rows) * ds, "transpose destination");
         break;
       case TASK_TRANSPOSE16:
-        if (t.cols != 64 || t.rows % 64 || t.rows > 256 || t.rows == 0 || ss != 2 || ds != 2 ||
-            t.src_off % 16 || t.dst_off % 16 || (t.src_ld * 2) % 16 || (t.dst_ld * 2) % 16)
+      case TASK_TRANSPOSE4: {
+        const uint32_t E = t.kind == TASK_TRANSPOSE16 ? 64 : 32;
+        const bool types = E == 64 ? ss == 2 && ds == 2 : (ss == 4 && ds >= 2) || (ds == 4 && ss >= 2);
+        if (!types || t.cols != E || t.rows % E || t.rows > 4 * E || t.src_off % ss || t.dst_off % ds)
           fail(WB_EINVAL, "internal: bad register-transpose work item");
         inside(t.src_idx, t.src_off, (uint64_t(t.rows - 1) * t.src_ld + t.cols) * ss, "transpose source");
         inside(t.dst_idx, t.dst_off, (uint64_t(t.cols - 1) * t.dst_ld + t.rows) * ds, "transpose destination");
         break;
+      }
       default:
         fail(WB_EINVAL, "internal: unknown work item");
     }

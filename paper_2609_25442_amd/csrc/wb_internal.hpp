@@ -147,14 +147,18 @@ enum TaskKind : uint8_t {
   TASK_SCALAR = 3,     // any supported pair, element by element (rows narrower than a unit of TASK_ROWS)
   TASK_TRANSPOSE = 4,  // dst[c][r] = cvt(src[r][c]), one LDS tile of up to 64 x 64
   TASK_TRANSPOSE16 = 5,  // 2-byte dst[c][r] = src[r][c], (64..256) rows x 64 cols, in registers
+  TASK_TRANSPOSE4 = 8,   // the same with fp32 on a side, (32..128) rows x 32 cols
   TASK_ROWS = 7,       // any supported pair, rows of any element address and width (at least one unit)
-  TASK_TILE = 6,       // 2-byte dst[c][r] = src[r][c], one kTileRows x kTileCols tile through LDS (a launch of its own)
+  TASK_TILE = 6,       // dst[c][r] = src[r][c], one kTileRows x tile_cols tile through LDS (a launch of its own)
 };
 
 // TASK_TILE items run one per workgroup of kTileThreads threads: each thread
-// transposes one 8 x 8 sub-tile, so that a wave instruction reads 1 KiB of one
-// source row and writes 256 bytes of each of four destination rows.
-constexpr int kTileRows = 128, kTileCols = 512;  // of the source block
+// transposes one 8 x 8 sub-tile of 2-byte elements, so that a wave instruction
+// reads 1 KiB of one source row and writes 256 bytes of each of four
+// destination rows; 4-byte tiles are half as many columns wide (1 KiB again,
+// and 512 bytes of two destination rows).
+constexpr int kTileRows = 128, kTileCols = 512;  // of the source block, 2-byte elements
+constexpr int tile_cols(int es) { return kTileCols * 2 / es; }
 constexpr int kTileThreads = (kTileRows / 8) * (kTileCols / 8);
 
 struct Task {
@@ -188,7 +192,7 @@ inline uint32_t rows_units(int sdt, int ddt, uint64_t dst_off, uint64_t dst_ld, 
 // threads (a multiple of 64: one wave by default) per item, one per chunk of
 // kChunkVecs 16-byte vectors (kChunkPerLane per lane); class 1 (transposes)
 // takes 2^shift[1] per item, TASK_TRANSPOSE16 one per kChunkThreads / 64 tiles
-// of 64 x 64 and TASK_TRANSPOSE one per 32 x 32 quarter of its tile; class 2
+// of 64 x 64 (TASK_TRANSPOSE4 32 x 32) and TASK_TRANSPOSE one per 32 x 32 quarter of its tile; class 2
 // (element-wise) one workgroup per item. Grids wider than kMaxGridX
 // workgroups fold into a second dimension.
 #ifndef WB_CHUNK_THREADS
@@ -205,7 +209,7 @@ static_assert(kChunkThreads % 64 == 0 && kChunkThreads <= 256, "copy workgroup s
 
 inline int task_class(const Task& t) {
   if (t.kind == TASK_TILE) return 3;
-  if (t.kind == TASK_TRANSPOSE || t.kind == TASK_TRANSPOSE16) return 1;
+  if (t.kind == TASK_TRANSPOSE || t.kind == TASK_TRANSPOSE16 || t.kind == TASK_TRANSPOSE4) return 1;
   return t.kind == TASK_SCALAR ? 2 : 0;
 }
 
@@ -223,8 +227,10 @@ inline uint32_t task_chunks(const Task& t) {
       const uint64_t units = uint64_t(t.rows) * t.units;  // one per lane
       return static_cast<uint32_t>((units + kChunkThreads - 1) / kChunkThreads);
     }
-    case TASK_TRANSPOSE16: {
-      const uint32_t per = kChunkThreads / 64, tiles = (t.rows + 63) / 64;
+    case TASK_TRANSPOSE16:
+    case TASK_TRANSPOSE4: {
+      const uint32_t edge = t.kind == TASK_TRANSPOSE16 ? 64 : 32;
+      const uint32_t per = kChunkThreads / 64, tiles = (t.rows + edge - 1) / edge;
       return (tiles + per - 1) / per;
     }
     case TASK_TRANSPOSE: return 4;
