@@ -39,6 +39,22 @@ def test_make_ids_matches_oracle(dtype):
         assert np.array_equal(_codes(t, dtype), id_chunk(ids, k, 16)), k
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [1, 3, 4, 7, 8, 9, 2047, 2049, 70_001])
+def test_make_ids_any_address_and_size(dtype, n):
+    """Partial vectors, destinations at any element, chunk wrap-arounds inside
+    a vector; nothing written outside."""
+    first = (1 << 32) - 5
+    ids = first + np.arange(n, dtype=np.int64)
+    for off in (0, 1, 3):
+        for k in range(3):
+            big = torch.full((n + 16,), 1.0, dtype=TORCH[dtype], device="cuda")
+            wb.make_ids(big[off:off + n], dtype, first, k)
+            torch.cuda.synchronize()
+            assert np.array_equal(_codes(big[off:off + n], dtype), id_chunk(ids, k, 16)), (off, k)
+            assert bool((big[:off] == 1.0).all()) and bool((big[off + n:] == 1.0).all()), (off, k)
+
+
 def _field(rng, R, C, kind):
     if kind == "random":
         return rng.integers(0, 1 << 16, size=(R, C))
