@@ -3,7 +3,7 @@ arXiv 2609.25442, Sec. 3.1-3.2): layouts as slice-copy source maps, the
 routing plan, and the packing and assembly kernels.
 
 Argument marshalling only: every step runs in libwb.so (host planner in C++,
-kernels in HIP). Importing this package fails if the library is not built
+kernels in HIP); the checks of a call's tensors run in _args.so. Importing this package fails if the library is not built
 (``python paper_2609_25442_amd/build.py``); there is no fallback path.
 """
 
@@ -13,6 +13,7 @@ import atexit
 import collections.abc
 import ctypes
 import os
+import struct
 import weakref
 from ctypes import POINTER, byref, c_char_p, c_int32, c_int64, c_size_t, c_uint32, c_uint64, c_void_p
 
@@ -157,6 +158,7 @@ def _load():
 
 
 lib = _load()
+from . import _args  # noqa: E402  (built with libwb.so; needs torch's libraries, loaded above)
 
 
 def _check(rc: int):
@@ -197,7 +199,8 @@ def _stream_handle(stream) -> int | None:
     if stream is None:
         import torch
 
-        return torch.cuda.current_stream().cuda_stream
+        # the address alone: current_stream() makes a Stream object of it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -232,6 +235,15 @@ def _check_buffer(x, nbytes: int, what: str):
     _check_memory(x, what)
     if not isinstance(x, int) and x is not None and x.numel() * x.element_size() < nbytes:
         _einval(f"{what} is smaller than the plan needs ({x.numel() * x.element_size()} < {nbytes} bytes)")
+
+
+def _buffer_ptr(x, nbytes: int, what: str):
+    """Address of a buffer of at least ``nbytes`` bytes, after its checks."""
+    p = _args.address(x, nbytes)
+    if p is None:  # no plain GPU tensor of that size: the full checks decide
+        _check_buffer(x, nbytes, what)
+        p = _ptr(x)
+    return p
 
 
 class Layout:
@@ -339,6 +351,8 @@ class Plan:
         self.role, self.rank = role, rank
         self._workspace = None
         self._locals = None
+        self._expect = None
+        self._sizes = {}
 
     def _i64(self, fn):
         v = c_int64()
@@ -403,26 +417,44 @@ class Plan:
                         f"{'smaller' if x.numel() < numel else 'larger'} than the plan's {numel}")
             _check_memory(x, f"{what} {i}")
 
+    def _local_ptrs(self, xs, what: str):
+        """The pointer table of a call, after the checks of its tensors."""
+        if self._expect is None:
+            dts = [self.local_tensor(i) for i in range(self.num_local_tensors)]
+            self._expect = b"".join(struct.pack("qq", numel, DTYPES[dt]) for dt, numel in dts)
+        ptrs = (c_void_p * max(1, len(xs)))()
+        if not _args.pointers(xs, self._expect, ctypes.addressof(ptrs)):
+            self._check_locals(xs, what)
+            ptrs = (c_void_p * max(1, len(xs)))(*[_ptr(x) for x in xs])
+        return ptrs
+
+    def _size(self, key):
+        """A buffer size of the plan (which never changes): of a round, of
+        (round, stage) of the forward buffer, or the largest round's (None)."""
+        n = self._sizes.get(key)
+        if n is None:
+            n = (self.buffer_bytes if key is None else self.forward_bytes(key[1], key[0]) if isinstance(key, tuple)
+                 else self.round_buffer_bytes(key))
+            self._sizes[key] = n
+        return n
+
     def pack_round(self, rnd, src, send_buf, stream=None):
-        self._check_locals(src, "local tensor")
-        _check_buffer(send_buf, self.round_buffer_bytes(rnd), "send_buf")
-        ptrs = (c_void_p * max(1, len(src)))(*[_ptr(x) for x in src])
-        _check(lib.wb_pack_round(self._h, rnd, ptrs, _ptr(send_buf), _stream_handle(stream)))
+        ptrs = self._local_ptrs(src, "local tensor")
+        buf = _buffer_ptr(send_buf, self._size(rnd), "send_buf")
+        _check(lib.wb_pack_round(self._h, rnd, ptrs, buf, _stream_handle(stream)))
 
     def unpack_round(self, rnd, recv_buf, dst, stream=None):
-        self._check_locals(dst, "local tensor")
-        _check_buffer(recv_buf, self.round_buffer_bytes(rnd), "recv_buf")
-        ptrs = (c_void_p * max(1, len(dst)))(*[_ptr(x) for x in dst])
-        _check(lib.wb_unpack_round(self._h, rnd, _ptr(recv_buf), ptrs, _stream_handle(stream)))
+        ptrs = self._local_ptrs(dst, "local tensor")
+        buf = _buffer_ptr(recv_buf, self._size(rnd), "recv_buf")
+        _check(lib.wb_unpack_round(self._h, rnd, buf, ptrs, _stream_handle(stream)))
 
     def unpack_round_noalloc(self, rnd, recv_buf, dst, stream=None):
         """unpack_round without a workspace or upload: the library stages the
         round's tables in its own per-GPU device array (calls that overlap on
         one GPU race; a round whose tables exceed the array raises WB_ESIZE)."""
-        self._check_locals(dst, "local tensor")
-        _check_buffer(recv_buf, self.round_buffer_bytes(rnd), "recv_buf")
-        ptrs = (c_void_p * max(1, len(dst)))(*[_ptr(x) for x in dst])
-        _check(lib.wb_unpack_round_noalloc(self._h, rnd, _ptr(recv_buf), ptrs, _stream_handle(stream)))
+        ptrs = self._local_ptrs(dst, "local tensor")
+        buf = _buffer_ptr(recv_buf, self._size(rnd), "recv_buf")
+        _check(lib.wb_unpack_round_noalloc(self._h, rnd, buf, ptrs, _stream_handle(stream)))
 
     @property
     def node_size(self) -> int:
@@ -452,10 +484,10 @@ class Plan:
         return v.value
 
     def forward_round(self, rnd, stage, recv_buf, fwd_buf, stream=None):
-        _check_buffer(recv_buf, self.round_buffer_bytes(rnd), "recv_buf")
-        _check_buffer(fwd_buf, self.forward_bytes(stage, rnd), "fwd_buf")
-        _check(lib.wb_forward_round(self._h, rnd, stage, _ptr(recv_buf), _ptr(fwd_buf) if fwd_buf is not None else 0,
-                                    _stream_handle(stream)))
+        recv = _buffer_ptr(recv_buf, self._size(rnd), "recv_buf")
+        size = self._size((rnd, stage))
+        fwd = _buffer_ptr(fwd_buf, size, "fwd_buf") if fwd_buf is not None else 0
+        _check(lib.wb_forward_round(self._h, rnd, stage, recv, fwd, _stream_handle(stream)))
 
     def rank_buffer_bytes(self, role: int, rank: int) -> int:
         v = c_int64()
@@ -522,16 +554,14 @@ class Plan:
         self._workspace = workspace
 
     def pack(self, src, send_buf, stream=None):
-        self._check_locals(src, "local tensor")
-        _check_buffer(send_buf, self.buffer_bytes, "send_buf")
-        ptrs = (c_void_p * max(1, len(src)))(*[_ptr(x) for x in src])
-        _check(lib.wb_pack(self._h, ptrs, _ptr(send_buf), _stream_handle(stream)))
+        ptrs = self._local_ptrs(src, "local tensor")
+        buf = _buffer_ptr(send_buf, self._size(None), "send_buf")
+        _check(lib.wb_pack(self._h, ptrs, buf, _stream_handle(stream)))
 
     def unpack(self, recv_buf, dst, stream=None):
-        self._check_locals(dst, "local tensor")
-        _check_buffer(recv_buf, self.buffer_bytes, "recv_buf")
-        ptrs = (c_void_p * max(1, len(dst)))(*[_ptr(x) for x in dst])
-        _check(lib.wb_unpack(self._h, _ptr(recv_buf), ptrs, _stream_handle(stream)))
+        ptrs = self._local_ptrs(dst, "local tensor")
+        buf = _buffer_ptr(recv_buf, self._size(None), "recv_buf")
+        _check(lib.wb_unpack(self._h, buf, ptrs, _stream_handle(stream)))
 
     def __del__(self):
         # at interpreter teardown the module's globals may already be gone

@@ -1,4 +1,5 @@
-"""Build libwb.so in-tree: host C++ with g++, gfx950 kernels with hipcc.
+"""Build libwb.so in-tree: host C++ with g++, gfx950 kernels with hipcc; and
+_args.so, the binding's argument checks (against torch's headers).
 
 Run as ``python paper_2609_25442_amd/build.py`` (by path: importing the package
 needs the library). Always recompiles.
@@ -6,14 +7,17 @@ needs the library). Always recompiles.
 
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libwb.so")
+ARGS = os.path.join(HERE, "_args.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.path.join(ROCM, "bin", "hipcc")
 
@@ -34,6 +38,17 @@ def _run(cmd):
     return r
 
 
+def build_args() -> str:
+    """Compile and link the binding's extension module."""
+    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    inc, lib = os.path.join(torch, "include"), os.path.join(torch, "lib")
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-isystem", inc, "-isystem",
+          os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "args.cpp"), "-o", ARGS + ".tmp", "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    os.replace(ARGS + ".tmp", ARGS)
+    return ARGS
+
+
 def build(verbose: bool = False, out: str = OUT, defines=()) -> str:
     """Compile and link libwb.so at ``out``; ``defines`` are extra -D flags for
     the host and device sources (tuning knobs such as WB_CHUNK_PER_LANE)."""
@@ -51,6 +66,8 @@ def build(verbose: bool = False, out: str = OUT, defines=()) -> str:
     tmp = out + ".tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, out)
+    if out == OUT:
+        build_args()
     if verbose:
         print("built", out)
     return out
