@@ -56,12 +56,11 @@ constexpr int kFlatUnroll = 8;  // vectors in flight per lane (FLAT)
 // byte address).
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 
-// A thread writes 16 bytes at a time: 8 bf16 or 4 fp32 chunks. Bound: HBM
-// write (5.8 TB/s for a stream of plain 16-byte stores); the stores are plain
-// because the loader reads the identifiers next. One 2-byte store per lane ran
-// at 4.1 TB/s (the identifiers of a 2.8e9-element bf16 checkpoint in 75
-// tensors, two chunks: 2.70 ms), so this at 4.9 (2.27 ms; 5.2 for its largest
-// tensor).
+// A thread writes 16 bytes: 8 bf16 or 4 fp32 chunks, one workgroup per 4 KiB up
+// to 2^22 workgroups. Bound: HBM write; the stores are plain because the
+// loader reads the identifiers next. 1.05 GB of bf16: 6.9 TB/s one shot, 6.3
+// with 2^16 looping workgroups, 5.2 with 2^14 (5.4 with non-temporal stores)
+// and 4.5 with 2^12; one 2-byte store per lane of 2^16 reached 4.1.
 template <bool kF32>
 __global__ __launch_bounds__(kThreads) void wb_make_ids_kernel(char* dst, int64_t numel, int64_t first_id, int shift,
                                                                uint32_t mask) {
@@ -812,7 +811,7 @@ dim3 strided_grid(int64_t xtiles, int64_t strips) {
 int launch_make_ids(void* dst, int dtype, int64_t numel, int64_t first_id, int shift, uint32_t mask, void* stream) {
   if (numel == 0) return hipSuccess;
   const int64_t per = kThreads * (dtype == WB_F32 ? 4 : 8), want = (numel + per - 1) / per;
-  const dim3 grid(static_cast<unsigned>(want < 16384 ? want : 16384));
+  const dim3 grid(static_cast<unsigned>(want < (1 << 22) ? want : 1 << 22));
   if (dtype == WB_F32)
     hipLaunchKernelGGL(wb_make_ids_kernel<true>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream),
                        static_cast<char*>(dst), numel, first_id, shift, mask);
