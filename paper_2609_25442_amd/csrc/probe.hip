@@ -458,6 +458,9 @@ __device__ __forceinline__ void load_row_vec(const Passes<P>& s, int64_t rowoff,
 // rows loaded and then computed: carry passes (one pass, int) 5-7 % faster
 // per pass than one row and faster than two or four rows; held passes (three,
 // int64) 9.56 -> 8.05 ms for 48 GB; two rows ahead gave nothing more.
+// A lane's differences are tested by one OR, and rows go in pairs so that
+// loads and the last two rows' h change places instead of being moved: the
+// arithmetic per element bounded the passes before HBM did.
 template <int V, typename T, int P, int S, class Out>
 __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64_t cols, int64_t base, int64_t i0,
                                          int64_t vb, const Out& out) {
@@ -469,9 +472,9 @@ __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64
   const int64_t i1 = i0 + S < rows ? i0 + S : rows;
   const int64_t rb = cols * (16 / V);
   const bool left = lane == 0 && j0 >= 2;
-  T h1[V], h2[V];
+  T ha[V], hb[V];  // h of the last two rows
 #pragma unroll
-  for (int k = 0; k < V; ++k) h1[k] = h2[k] = 0;
+  for (int k = 0; k < V; ++k) ha[k] = hb[k] = 0;
   const int64_t ist = i0 >= 2 ? i0 - 2 : 0;
   auto fetch = [&](int64_t i, uint4* qq, uint2* ll) {
 #pragma unroll
@@ -487,13 +490,8 @@ __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64
       }
     }
   };
-  uint4 q[P];
-  uint2 lq[P];
-  fetch(ist, q, lq);
-  for (int64_t i = ist; i < i1; ++i) {
-    uint4 qn[P];
-    uint2 ln[P];
-    fetch(i + 1, qn, ln);
+  // row i from its vectors; h1 is h(i - 1), h2 is h(i - 2) and becomes h(i)
+  auto row = [&](int64_t i, const uint4* q, const uint2* lq, const T* h1, T* h2) {
     T x[V];
 #pragma unroll
     for (int k = 0; k < V; ++k) x[k] = 0;
@@ -515,26 +513,31 @@ __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64
       p1 = l1;
       p2 = l2;
     }
-    T h[V];
-    h[0] = x[0] - 2 * p1 + p2;
-    h[1] = x[1] - 2 * x[0] + p1;
-#pragma unroll
-    for (int k = 2; k < V; ++k) h[k] = x[k] - 2 * x[k - 1] + x[k - 2];
-    T d[V];
-    unsigned any = 0;
+    T d[V], nz = 0;
 #pragma unroll
     for (int k = 0; k < V; ++k) {
-      d[k] = h[k] - 2 * h1[k] + h2[k];
-      h2[k] = h1[k];
-      h1[k] = h[k];
-      any |= (live && i >= i0 && d[k] != 0) ? (1u << k) : 0u;
+      const T y1 = k >= 1 ? x[k - 1] : p1, y2 = k >= 2 ? x[k - 2] : k == 1 ? p1 : p2;
+      const T h = x[k] - 2 * y1 + y2;
+      d[k] = h - 2 * h1[k] + h2[k];
+      h2[k] = h;
+      nz |= d[k];
     }
-    if (__ballot(any != 0) != 0) out.template put_row<V>(any, base + i * cols + j0, d, lane);
+    if (i >= i0 && __ballot(live && nz != 0) != 0) {
+      unsigned any = 0;
 #pragma unroll
-    for (int c = 0; c < P; ++c) {
-      q[c] = qn[c];
-      lq[c] = ln[c];
+      for (int k = 0; k < V; ++k) any |= (live && d[k] != 0) ? (1u << k) : 0u;
+      out.template put_row<V>(any, base + i * cols + j0, d, lane);
     }
+  };
+  uint4 qa[P], qb[P];
+  uint2 la[P], lb[P];
+  fetch(ist, qa, la);
+  for (int64_t i = ist; i < i1; i += 2) {
+    fetch(i + 1, qb, lb);
+    row(i, qa, la, hb, ha);
+    if (i + 1 >= i1) break;
+    fetch(i + 2, qa, la);
+    row(i + 1, qb, lb, ha, hb);
   }
 }
 
@@ -569,10 +572,13 @@ __device__ __forceinline__ void flat_tile(const Passes<P>& s, int64_t cols, int6
     d[1] = x[u][1] - 2 * x[u][0] + p1;
 #pragma unroll
     for (int k = 2; k < V; ++k) d[k] = x[u][k] - 2 * x[u][k - 1] + x[u][k - 2];
+    T nz = 0;
+#pragma unroll
+    for (int k = 0; k < V; ++k) nz |= d[k];
+    if (__ballot(v < nvec && nz != 0) == 0) continue;
     unsigned any = 0;
 #pragma unroll
     for (int k = 0; k < V; ++k) any |= (v < nvec && d[k] != 0) ? (1u << k) : 0u;
-    if (__ballot(any != 0) == 0) continue;
     out.template put_row<V>(any, base + v * V, d, lane);
   }
 }
@@ -623,11 +629,16 @@ __global__ __launch_bounds__(kThreads) void wb_diff2_flat_kernel(const char* __r
   out.flush();
 }
 
-// Batched launches: workgroup b takes tile b of the table, taller VEC tiles
-// (vec_tile) and FLAT tiles of several sub-tiles (fewer, larger table
-// rows). Held passes recombine up to kMaxPasses passes in int64; carry passes
-// read one pass in int.
-constexpr int kBatchVecStrip = 128;
+// Batched launches: workgroup b takes tile b of the table, VEC tiles (vec_tile)
+// of kBatchVecStrip rows and FLAT tiles of several sub-tiles (fewer, larger
+// table rows). Held passes recombine up to kMaxPasses passes in int64; carry
+// passes read one pass in int. Bound: HBM reads in flight; a TP2 rank of an
+// 8-layer 8 B model (2.8 GB of bf16 a pass) in strips of 128 rows 574, 557
+// with vec_tile's pairs of rows; of 64, 32 and 16 rows 546, 519 and 535 us
+// (5.4 TB/s): shorter strips even out the launch's end until the two halo rows
+// cost more. With non-temporal loads 620, with the XCD-aware order of the copy
+// launches 531, with registers for two more waves a SIMD (spills) 780.
+constexpr int kBatchVecStrip = 32;
 constexpr int kBatchFlatUnroll = 4;
 constexpr int kBatchFlatSub = 8;  // sub-tiles of kBatchFlatUnroll x kThreads vectors per FLAT tile
 
