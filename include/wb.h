@@ -492,9 +492,9 @@ int wb_diff2_batch_workspace(const wb_field* fields, int32_t n, size_t* bytes);
  * plus i * cols_f + j. index, value (8-byte aligned), capacity and count as
  * for wb_diff2 (count is the total over all fields). workspace is device
  * memory of at least wb_diff2_batch_workspace bytes, 8-byte aligned, owned by
- * the caller; the call copies the tile table into it on `stream` and waits
- * for that copy (so it returns after the stream's earlier work), and the
- * workspace must stay untouched until the launch has run. Errors: WB_EINVAL
+ * the caller; launches on `stream` write the tables into it (one per 56
+ * fields; the call does not wait), and the workspace must stay untouched
+ * until the launch has run. Errors: WB_EINVAL
  * (null, misaligned, bad field, workspace too small, more than 2^31 - 1
  * tiles), WB_EHIP. */
 int wb_diff2_batch(const wb_field* fields, int32_t n, void* workspace, size_t workspace_bytes, int64_t* index,
@@ -529,9 +529,9 @@ int wb_diff2_carry_workspace(const wb_field* fields, int32_t n, int64_t carry_ca
  * workspace, same fields). workspace: device memory of at least
  * wb_diff2_carry_workspace bytes, 8-byte aligned, owned by the caller, the
  * same buffer with the same carry_capacity for every pass of one probe (it
- * holds the carries between passes). The call copies the tile table into it
- * on `stream` and waits for that copy. Passes on one workspace must not
- * overlap. Six launches at most; the stencil reads each element about once.
+ * holds the carries between passes). Launches on `stream` write the tables
+ * into it (one per 56 fields; the call does not wait). Passes on one
+ * workspace must not overlap. Five more launches at most; the stencil reads each element about once.
  * Errors: as for wb_diff2_batch, and WB_EINVAL for a field of more than one
  * pass, a negative pass, a null or misaligned carries, carry_capacity outside
  * 1..2^36. */

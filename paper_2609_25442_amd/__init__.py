@@ -645,9 +645,10 @@ def _field_array(fields):
         ts = list(ts) if isinstance(ts, (list, tuple)) else [ts]
         if not 1 <= len(ts) <= 3:
             raise ValueError("a field holds 1 to 3 passes")
-        arr[f].dtype, arr[f].passes, arr[f].rows, arr[f].cols = DTYPES[dtype], len(ts), rows, cols
+        x = arr[f]
+        x.dtype, x.passes, x.rows, x.cols = DTYPES[dtype], len(ts), rows, cols
         for c, t in enumerate(ts):
-            arr[f].data[c] = _ptr(t)
+            x.data[c] = _ptr(t)
     return arr
 
 
@@ -738,14 +739,14 @@ def _carry_entries(fields, k, last, st, device):
     import torch
 
     while True:
-        diff2_carry(fields, k, last, st["cap"], st["idx"], st["val"], st["count"], st["carries"], st["ws"])
-        n, c = int(st["count"].item()), int(st["carries"].item())
+        diff2_carry(fields, k, last, st["cap"], st["entries"][0], st["entries"][1], st["n"][:1], st["n"][1:], st["ws"])
+        n, c = st["n"].tolist()
         if c > st["cap"]:
             raise _CarryRoom(c)
-        if n <= st["idx"].numel():
-            return st["idx"][:n].cpu().numpy(), st["val"][:n].cpu().numpy(), c
-        st["idx"] = torch.empty(n, dtype=torch.int64, device=device)
-        st["val"] = torch.empty(n, dtype=torch.int64, device=device)
+        if n <= st["entries"].shape[1]:
+            idx, val = st["entries"][:, :n].cpu().numpy()
+            return idx, val, c
+        st["entries"] = torch.empty((2, n), dtype=torch.int64, device=device)
 
 
 def _record_split(probe, chunk, offsets, index, value):
@@ -884,15 +885,13 @@ def _probe_rank(catalog, ckpt_dtype, tdt, load, r, names, device, stats, hold_pa
             # back checkpoint tensors, which the next pass overwrites
             held.append([x.clone() for x in locs] if not last else locs)
         else:
-            fields = [(x, ckpt_dtype, b * rr, cc) for x, (b, rr, cc) in zip(locs, shapes)]
+            fields = _field_array([(x, ckpt_dtype, b * rr, cc) for x, (b, rr, cc) in zip(locs, shapes)])
             if carry is None:
                 cap = carry_capacity or 16 * (int(offsets[-1]) >> 16) + 64 * len(fields) + 4096
                 nbytes = diff2_carry_workspace(fields, cap)
                 carry = {"cap": cap, "ws": torch.empty(nbytes, dtype=torch.uint8, device=device),
-                         "idx": torch.empty(1 << 16, dtype=torch.int64, device=device),
-                         "val": torch.empty(1 << 16, dtype=torch.int64, device=device),
-                         "count": torch.zeros(1, dtype=torch.int64, device=device),
-                         "carries": torch.zeros(1, dtype=torch.int64, device=device)}
+                         "entries": torch.empty((2, 1 << 16), dtype=torch.int64, device=device),
+                         "n": torch.zeros(2, dtype=torch.int64, device=device)}
             idx, val, carries = _carry_entries(fields, k, last, carry, device)
             _record_split(probe, k, offsets, idx, val)
             entries = len(idx)

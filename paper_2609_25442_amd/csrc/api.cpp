@@ -920,14 +920,22 @@ int wb_diff2(const void* src, int32_t dtype, int64_t rows, int64_t cols, int64_t
   });
 }
 
-// Check the fields of a batched diff2 call and build its field and tile
-// tables; the device extents of the fields are checked only when `memory` is
-// set. The workspace holds the field table, then (8-byte aligned) the tiles.
+// Check the fields of a batched diff2 call and count its tiles; the device
+// extents of the fields are checked only when `memory` is set. The workspace
+// holds the field table, then (8-byte aligned) the tiles, both written by a
+// launch.
 struct Diff2Tables {
   std::vector<wb::DiffField> fields;
-  std::vector<wb::DiffTile> tiles;
+  std::vector<int64_t> first{0};  // first tile of each field; the number of tiles last
+  int64_t ntiles() const { return first.back(); }
   size_t tiles_offset() const { return (fields.size() * sizeof(wb::DiffField) + 7) / 8 * 8; }
-  size_t bytes() const { return tiles.empty() ? 0 : tiles_offset() + tiles.size() * sizeof(wb::DiffTile); }
+  size_t end() const { return tiles_offset() + ntiles() * sizeof(wb::DiffTile); }
+  size_t bytes() const { return ntiles() ? end() : 0; }
+  int write(char* ws, void* stream) const {
+    return wb::launch_diff_tables(fields.data(), first.data(), static_cast<int32_t>(fields.size()),
+                                  reinterpret_cast<wb::DiffField*>(ws),
+                                  reinterpret_cast<wb::DiffTile*>(ws + tiles_offset()), stream);
+  }
 };
 
 static int diff2_batch_tables(const wb_field* fields, int32_t n, bool memory, Diff2Tables& T) {
@@ -961,11 +969,11 @@ static int diff2_batch_tables(const wb_field* fields, int32_t n, bool memory, Di
         if (rc != WB_OK) return rc;
       }
     }
-    wb::diff_tiles(fi, f, T.tiles);
+    T.first.push_back(T.ntiles() + wb::diff_tiles(f));
+    if (T.ntiles() > INT32_MAX) return set_error(WB_EINVAL, "more than 2^31 - 1 tiles");
     T.fields.push_back(f);
     base += numel;
   }
-  if (T.tiles.size() > size_t(INT32_MAX)) return set_error(WB_EINVAL, "more than 2^31 - 1 tiles");
   return WB_OK;
 }
 
@@ -994,22 +1002,16 @@ int wb_diff2_batch(const wb_field* fields, int32_t n, void* workspace, size_t wo
     if (rc != WB_OK) return rc;
     const size_t need = T.bytes();
     if (need > workspace_bytes) return set_error(WB_EINVAL, "workspace smaller than wb_diff2_batch_workspace");
-    hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
     if (need > 0) {
       rc = check_extent(workspace, static_cast<int64_t>(need), "workspace", 8);
       if (rc != WB_OK) return rc;
-      std::vector<char> host(need);
-      std::memcpy(host.data(), T.fields.data(), T.fields.size() * sizeof(wb::DiffField));
-      std::memcpy(host.data() + T.tiles_offset(), T.tiles.data(), T.tiles.size() * sizeof(wb::DiffTile));
-      hipError_t e = hipMemcpyAsync(ws, host.data(), need, hipMemcpyHostToDevice, st);
-      if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (diff2 tables)");
-      e = hipStreamSynchronize(st);  // the host copy is freed on return
-      if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+      const int e = T.write(ws, stream);
+      if (e != 0) return set_error(WB_EHIP, std::string("diff2 tables: ") + wb::hip_error_string(e));
     }
     const int e = wb::launch_diff2_batch(reinterpret_cast<const wb::DiffField*>(ws),
                                          reinterpret_cast<const wb::DiffTile*>(ws + T.tiles_offset()),
-                                         int64_t(T.tiles.size()), index, value, capacity,
+                                         T.ntiles(), index, value, capacity,
                                          reinterpret_cast<unsigned long long*>(count), stream);
     if (e != 0) return set_error(WB_EHIP, std::string("diff2 launch: ") + wb::hip_error_string(e));
     return WB_OK;
@@ -1033,14 +1035,14 @@ static CarryLayout carry_layout(const Diff2Tables& T, int64_t capacity) {
   CarryLayout L;
   L.slots = 64;
   while (L.slots < uint64_t(2 * capacity)) L.slots <<= 1;
-  const size_t tables = T.tiles_offset() + T.tiles.size() * sizeof(wb::DiffTile);
+  const size_t tables = T.end();
   L.counters = (tables + 255) / 256 * 256;
   const size_t one = L.slots * 16;
   L.table[0] = L.counters + 2048;
   L.table[1] = L.table[0] + one;
   L.stage = L.table[1] + one;
-  L.stage_n = L.stage + T.tiles.size() * wb::kCarryStage * 16;
-  L.bytes = L.stage_n + (T.tiles.size() * 4 + 255) / 256 * 256;
+  L.stage_n = L.stage + T.ntiles() * wb::kCarryStage * 16;
+  L.bytes = L.stage_n + (T.ntiles() * 4 + 255) / 256 * 256;
   return L;
 }
 
@@ -1089,18 +1091,10 @@ int wb_diff2_carry(const wb_field* fields, int32_t n, int32_t pass, int32_t last
     if (L.bytes > workspace_bytes) return set_error(WB_EINVAL, "workspace smaller than wb_diff2_carry_workspace");
     rc = check_extent(workspace, static_cast<int64_t>(L.bytes), "workspace", 8);
     if (rc != WB_OK) return rc;
-    hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
-    const size_t tables = T.tiles_offset() + T.tiles.size() * sizeof(wb::DiffTile);
     if (!T.fields.empty()) {
-      std::vector<char> host(tables);
-      std::memcpy(host.data(), T.fields.data(), T.fields.size() * sizeof(wb::DiffField));
-      if (!T.tiles.empty())
-        std::memcpy(host.data() + T.tiles_offset(), T.tiles.data(), T.tiles.size() * sizeof(wb::DiffTile));
-      hipError_t e = hipMemcpyAsync(ws, host.data(), tables, hipMemcpyHostToDevice, st);
-      if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (diff2 tables)");
-      e = hipStreamSynchronize(st);  // the host copy is freed on return
-      if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+      const int e = T.write(ws, stream);
+      if (e != 0) return set_error(WB_EHIP, std::string("diff2 tables: ") + wb::hip_error_string(e));
     }
     wb::CarryTable tab[2];
     for (int t = 0; t < 2; ++t) {
@@ -1115,7 +1109,7 @@ int wb_diff2_carry(const wb_field* fields, int32_t n, int32_t pass, int32_t last
     const wb::CarryTable& in = tab[(pass + 1) & 1];
     const int e = wb::launch_diff2_carry(reinterpret_cast<const wb::DiffField*>(ws), n,
                                          reinterpret_cast<const wb::DiffTile*>(ws + T.tiles_offset()),
-                                         int64_t(T.tiles.size()), pass > 0, last != 0, in, next, index, value,
+                                         T.ntiles(), pass > 0, last != 0, in, next, index, value,
                                          capacity, reinterpret_cast<unsigned long long*>(count),
                                          reinterpret_cast<unsigned long long*>(carries), stream);
     if (e != 0) return set_error(WB_EHIP, std::string("diff2 carry launch: ") + wb::hip_error_string(e));

@@ -800,6 +800,55 @@ __global__ __launch_bounds__(kThreads) void wb_carry_report_kernel(const int32_t
 
 __global__ void wb_zero_count_kernel(unsigned long long* count) { *count = 0; }
 
+// How a field is cut into tiles: strips of istep rows, each cut at multiples
+// of jstep columns (ELEM) or 16-byte vectors (VEC, FLAT) below jend.
+struct TileGrid {
+  int64_t istep, jstep, jend;
+  __host__ __device__ int64_t per_strip() const { return (jend + jstep - 1) / jstep; }
+};
+__host__ __device__ inline TileGrid tile_grid(const DiffField& f) {
+  const int64_t nvec = f.cols / (f.dtype == WB_F32 ? 4 : 8);
+  if (f.kind == DIFF_FLAT) return {1, int64_t(kThreads) * kBatchFlatUnroll * kBatchFlatSub, nvec};
+  if (f.kind == DIFF_VEC) return {kBatchVecStrip, kThreads, nvec};
+  return {kStrip, kThreads, f.cols};
+}
+
+// The field and tile tables of a batched launch, written on the device from
+// up to kTableFields fields in the kernel arguments (below their 4 KiB): one
+// thread per tile, its field found by bisection of the fields' first tiles.
+// One launch per kTableFields fields and no wait: built on the host, copied
+// and waited for, the tables of a rank with 51 fields and 21,000 tiles took 60
+// us more of a pass.
+constexpr int32_t kTableFields = 56;
+struct DiffTableArgs {
+  DiffField field[kTableFields];
+  int32_t first[kTableFields + 1];  // first tile of field k of these; the number of tiles last
+  int32_t n, field0;
+};
+static_assert(sizeof(DiffTableArgs) + 16 <= 4096, "kernel argument size");
+
+__global__ __launch_bounds__(kThreads) void wb_diff_tables_kernel(DiffField* fields, DiffTile* tiles,
+                                                                  DiffTableArgs a) {
+  const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+  if (i < a.n) fields[i] = a.field[i];
+  if (i >= a.first[a.n]) return;
+  int32_t lo = 0, hi = a.n;  // first[lo] <= i < first[hi]
+  while (hi - lo > 1) {
+    const int32_t mid = (lo + hi) / 2;
+    if (a.first[mid] <= i)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  const TileGrid g = tile_grid(a.field[lo]);
+  const int64_t k = i - a.first[lo], per = g.per_strip();
+  DiffTile t{};
+  t.field = a.field0 + lo;
+  t.i0 = k / per * g.istep;
+  t.j0 = k % per * g.jstep;
+  tiles[i] = t;
+}
+
 // VEC and FLAT tiles need whole 16-byte vectors in every pass.
 int tile_kind(const void* const* src, int passes, int dtype, int64_t rows, int64_t cols) {
   const int V = dtype == WB_F32 ? 4 : 8;
@@ -867,27 +916,31 @@ int launch_diff2(const void* src, int dtype, int64_t rows, int64_t cols, int64_t
   return hipGetLastError();
 }
 
-void diff_tiles(int32_t fi, DiffField& f, std::vector<DiffTile>& out) {
+int64_t diff_tiles(DiffField& f) {
   f.kind = static_cast<uint8_t>(tile_kind(f.src, f.passes, f.dtype, f.rows, f.cols));
-  if (f.rows == 0 || f.cols == 0) return;
-  const int64_t nvec = f.cols / (f.dtype == WB_F32 ? 4 : 8);
-  int64_t istep = kStrip, jstep = kThreads, jend = f.cols;
-  if (f.kind == DIFF_FLAT) {
-    istep = 1;
-    jstep = int64_t(kThreads) * kBatchFlatUnroll * kBatchFlatSub;
-    jend = nvec;
-  } else if (f.kind == DIFF_VEC) {
-    istep = kBatchVecStrip;
-    jend = nvec;
-  }
-  DiffTile t{};
-  t.field = fi;
-  for (int64_t i0 = 0; i0 < f.rows; i0 += istep)
-    for (int64_t j0 = 0; j0 < jend; j0 += jstep) {
-      t.i0 = i0;
-      t.j0 = j0;
-      out.push_back(t);
+  if (f.rows == 0 || f.cols == 0) return 0;
+  const TileGrid g = tile_grid(f);
+  return (f.rows + g.istep - 1) / g.istep * g.per_strip();
+}
+
+int launch_diff_tables(const DiffField* fields, const int64_t* first, int32_t n, DiffField* dev_fields,
+                       DiffTile* dev_tiles, void* stream) {
+  for (int32_t f0 = 0; f0 < n; f0 += kTableFields) {
+    DiffTableArgs a{};
+    a.n = n - f0 < kTableFields ? n - f0 : kTableFields;
+    a.field0 = f0;
+    for (int32_t k = 0; k < a.n; ++k) {
+      a.field[k] = fields[f0 + k];
+      a.first[k] = static_cast<int32_t>(first[f0 + k] - first[f0]);
     }
+    a.first[a.n] = static_cast<int32_t>(first[f0 + a.n] - first[f0]);
+    const int64_t threads = a.first[a.n] > a.n ? a.first[a.n] : a.n;
+    hipLaunchKernelGGL(wb_diff_tables_kernel, dim3(static_cast<unsigned>((threads + kThreads - 1) / kThreads)),
+                       dim3(kThreads), 0, static_cast<hipStream_t>(stream), dev_fields + f0, dev_tiles + first[f0], a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 int launch_diff2_batch(const DiffField* fields, const DiffTile* tiles, int64_t ntiles, int64_t* index, int64_t* value,

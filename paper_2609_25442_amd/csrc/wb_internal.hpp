@@ -442,8 +442,13 @@ void probe_scan(const wb_probe_t& P, wb_layout_t& out, int rank);
 int launch_make_ids(void* dst, int dtype, int64_t numel, int64_t first_id, int shift, uint32_t mask, void* stream);
 int launch_diff2(const void* src, int dtype, int64_t rows, int64_t cols, int64_t* index, int32_t* value,
                  int64_t capacity, unsigned long long* count, void* stream);
-// fills f.kind and appends the tiles of field f (index fi) to out
-void diff_tiles(int32_t fi, DiffField& f, std::vector<DiffTile>& out);
+// fills f.kind; the number of tiles of field f
+int64_t diff_tiles(DiffField& f);
+// writes the field table and the tiles of n fields (field f's from tile
+// first[f]; first[n] of them, below 2^31) to the device; the host arrays are
+// free on return
+int launch_diff_tables(const DiffField* fields, const int64_t* first, int32_t n, DiffField* dev_fields,
+                       DiffTile* dev_tiles, void* stream);
 int launch_diff2_batch(const DiffField* fields, const DiffTile* tiles, int64_t ntiles, int64_t* index, int64_t* value,
                        int64_t capacity, unsigned long long* count, void* stream);
 // one carry pass: clears `next` (unless last), runs the stencil over the

@@ -229,6 +229,34 @@ def test_diff2_batch_capacity_overflow_reports_the_count():
     assert len(got) == 10 and all(want[i] == v for i, v in got.items())
 
 
+@pytest.mark.parametrize("n", [56, 57, 113])
+def test_tables_of_many_fields(n):
+    """The field and tile tables are written 56 fields a launch: fields on both
+    sides of each cut, empty ones among them, and heights around a pair of rows
+    and a strip, in one batch of held passes and as carried passes, equal the
+    oracle's entries."""
+    rng = np.random.default_rng(n)
+    shapes = [(1, 16), (2, 16), (3, 24), (5, 13), (0, 8), (127, 8), (128, 8), (129, 16), (130, 8), (131, 7), (1, 999)]
+    fields_np = []
+    for k in range(n):
+        R, C = shapes[(k + n) % len(shapes)]
+        fields_np.append(([rng.integers(0, 1 << 16, size=(R, C)) for _ in range(2)], R, C))
+    fields = [([_to_gpu(x, "bf16") for x in F], "bf16", R, C) for F, R, C in fields_np]
+    want = _expected(fields_np)
+    say(f"[diff2 tables] batch of {n} fields")
+    count, got = _batch(fields, len(want) + 8)
+    assert count == len(want) and got == want
+    want, carried = _carry_expected(fields_np, 2)
+    numel = sum(R * C for _, R, C in fields_np)
+    runner = None
+    for k in range(2):
+        one = [(F[k], "bf16", R, C) for F, _, R, C in fields]
+        runner = runner or _CarryRun(one, numel + 16, numel + 16)
+        say(f"[diff2 tables] carry pass {k} of {n} fields")
+        count, c, got = runner.run(one, k, k == 1)
+        assert (count, c) == (len(want[k]), carried[k]) and got == want[k]
+
+
 def _carry_fields(rng, kind, passes):
     """Chunk fields of every shape (and a few empty ones): random chunks (a
     carry at nearly every position), or identifier slices whose bases sit
