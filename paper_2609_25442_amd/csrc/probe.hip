@@ -55,6 +55,34 @@ constexpr int kFlatUnroll = 8;  // vectors in flight per lane (FLAT)
 // Stores of 16 bytes at element alignment (gfx950 stores global memory at any
 // byte address).
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32_a2 __attribute__((aligned(2)));
+
+// A loaded tensor's address as a pointer to global memory: accesses through it
+// are no flat instructions, which wait with the lanes' shuffles on one counter
+// and are split at element alignment.
+__device__ __forceinline__ const char* global_ptr(const void* p) {
+  return (const char*)reinterpret_cast<const __attribute__((address_space(1))) char*>(reinterpret_cast<uintptr_t>(p));
+}
+
+// 16 bytes at element alignment.
+__device__ __forceinline__ uint4 load_vec(const char* p) {
+  const u32x4_a2 w = *reinterpret_cast<const u32x4_a2*>(p);
+  return uint4{w.x, w.y, w.z, w.w};
+}
+
+// Rows of RAGGED tiles are cut into vectors of V columns; the last one of
+// a row whose width is no multiple of V is moved left inside the row, and its
+// first `skip` columns belong to the vector before it.
+__host__ __device__ inline int64_t vec_count(int64_t cols, int V) { return (cols + V - 1) / V; }
+__device__ __forceinline__ int64_t vec_at(int64_t v, int64_t cols, int V, int& skip) {
+  const int64_t j0 = v * V < cols - V ? v * V : cols - V;
+  skip = static_cast<int>(v * V - j0 < V ? v * V - j0 : V);  // V: past the row's end
+  return j0;
+}
+// The bits of columns that are a vector's own.
+__device__ __forceinline__ unsigned own_columns(int skip) { return ~0u << skip; }
+
 
 // A thread writes 16 bytes: 8 bf16 or 4 fp32 chunks, one workgroup per 4 KiB up
 // to 2^22 workgroups. Bound: HBM write; the stores are plain because the
@@ -435,6 +463,21 @@ __device__ __forceinline__ void add_left_pair(const char* row, int64_t j0, int s
   }
 }
 
+// The values at columns j0 - 2 and j0 - 1 of a row (0 left of it), j0 >= 1, as
+// two uint16 (V = 8) or two words.
+template <int V>
+__device__ __forceinline__ uint2 load_left_pair(const char* row, int64_t j0) {
+  if (V == 8) {
+    if (j0 >= 2) return uint2{*reinterpret_cast<const u32_a2*>(row + (j0 - 2) * 2), 0u};
+    return uint2{uint32_t(*reinterpret_cast<const uint16_t*>(row)) << 16, 0u};
+  }
+  if (j0 >= 2) {
+    const u32x2_a2 w = *reinterpret_cast<const u32x2_a2*>(row + (j0 - 2) * 4);
+    return uint2{w.x, w.y};
+  }
+  return uint2{0u, *reinterpret_cast<const uint32_t*>(row)};
+}
+
 // Row i's vector at column j0 (x) and, for the first lane of a wavefront,
 // the two values left of it, summed over the passes.
 template <int V, typename T, int P>
@@ -461,17 +504,21 @@ __device__ __forceinline__ void load_row_vec(const Passes<P>& s, int64_t rowoff,
 // A lane's differences are tested by one OR, and rows go in pairs so that
 // loads and the last two rows' h change places instead of being moved: the
 // arithmetic per element bounded the passes before HBM did.
-template <int V, typename T, int P, int S, class Out>
+// kRagged: any width of at least a vector and any element address; the last
+// vector of a row is moved left inside it, and its lane loads the values left
+// of it as well. A kind of its own because the aligned rows lose with its code
+// (f32, 2.8 GB a pass: 750 -> 870 us).
+template <int V, typename T, int P, int S, bool kRagged, class Out>
 __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64_t cols, int64_t base, int64_t i0,
                                          int64_t vb, const Out& out) {
   const int lane = threadIdx.x & 63;
-  const int64_t nvec = cols / V;
   const int64_t v = vb + threadIdx.x;
-  const bool live = v < nvec;
-  const int64_t j0 = v * V;
+  const bool live = v < vec_count(cols, V);
+  int skip = 0;
+  const int64_t j0 = kRagged ? vec_at(v, cols, V, skip) : v * V;
   const int64_t i1 = i0 + S < rows ? i0 + S : rows;
   const int64_t rb = cols * (16 / V);
-  const bool left = lane == 0 && j0 >= 2;
+  const bool apart = lane == 0 || skip != 0, left = apart && j0 >= 1;
   T ha[V], hb[V];  // h of the last two rows
 #pragma unroll
   for (int k = 0; k < V; ++k) ha[k] = hb[k] = 0;
@@ -482,6 +529,11 @@ __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64
       qq[c] = uint4{0u, 0u, 0u, 0u};
       ll[c] = uint2{0u, 0u};
       if (c < s.n && live && i < i1) {
+        if (kRagged) {
+          qq[c] = load_vec(s.p[c] + j0 * (16 / V) + i * rb);
+          if (left) ll[c] = load_left_pair<V>(s.p[c] + i * rb, j0);
+          continue;
+        }
         qq[c] = *reinterpret_cast<const uint4*>(s.p[c] + j0 * (16 / V) + i * rb);
         if (left) {
           if (V == 8) ll[c].x = *reinterpret_cast<const uint32_t*>(s.p[c] + (j0 - 2) * 2 + i * rb);
@@ -509,7 +561,7 @@ __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64
       }
     }
     T p1 = __shfl_up(x[V - 1], 1, 64), p2 = __shfl_up(x[V - 2], 1, 64);
-    if (lane == 0) {
+    if (apart) {
       p1 = l1;
       p2 = l2;
     }
@@ -526,6 +578,7 @@ __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64
       unsigned any = 0;
 #pragma unroll
       for (int k = 0; k < V; ++k) any |= (live && d[k] != 0) ? (1u << k) : 0u;
+      if (kRagged) any &= own_columns(skip);
       out.template put_row<V>(any, base + i * cols + j0, d, lane);
     }
   };
@@ -599,7 +652,7 @@ __global__ __launch_bounds__(kThreads) void wb_diff2_kernel(const char* __restri
   out.flush();
 }
 
-template <int V>
+template <int V, bool kRagged>
 __global__ __launch_bounds__(kThreads) void wb_diff2_vec_kernel(const char* __restrict__ src, int64_t rows,
                                                                 int64_t cols, Sink<int> sink) {
   __shared__ WgBuf buf;
@@ -607,10 +660,10 @@ __global__ __launch_bounds__(kThreads) void wb_diff2_vec_kernel(const char* __re
   __syncthreads();
   const ListOut<int> out{&buf, sink};
   const Passes<1> s{{src}, 1};
-  const int64_t nvec = cols / V;
+  const int64_t nvec = vec_count(cols, V);
   for (int64_t vb = int64_t(blockIdx.x) * kThreads; vb < nvec; vb += int64_t(gridDim.x) * kThreads)
     for (int64_t i0 = int64_t(blockIdx.y) * kVecStrip; i0 < rows; i0 += int64_t(gridDim.y) * kVecStrip)
-      vec_tile<V, int, 1, kVecStrip>(s, rows, cols, 0, i0, vb, out);
+      vec_tile<V, int, 1, kVecStrip, kRagged>(s, rows, cols, 0, i0, vb, out);
   out.flush();
 }
 
@@ -646,7 +699,7 @@ template <typename T, int P, class Out>
 __device__ __forceinline__ void batch_tile(const DiffField& f, const DiffTile& t, const Out& out) {
   Passes<P> s;
 #pragma unroll
-  for (int c = 0; c < P; ++c) s.p[c] = static_cast<const char*>(f.src[c]);
+  for (int c = 0; c < P; ++c) s.p[c] = global_ptr(f.src[c]);
   s.n = P == 1 ? 1 : f.passes;
   if (f.kind == DIFF_FLAT) {
     for (int q = 0; q < kBatchFlatSub; ++q) {
@@ -658,9 +711,14 @@ __device__ __forceinline__ void batch_tile(const DiffField& f, const DiffTile& t
     }
   } else if (f.kind == DIFF_VEC) {
     if (f.dtype == WB_F32)
-      vec_tile<4, T, P, kBatchVecStrip>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
+      vec_tile<4, T, P, kBatchVecStrip, false>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
     else
-      vec_tile<8, T, P, kBatchVecStrip>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
+      vec_tile<8, T, P, kBatchVecStrip, false>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
+  } else if (f.kind == DIFF_RAGGED) {
+    if (f.dtype == WB_F32)
+      vec_tile<4, T, P, kBatchVecStrip, true>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
+    else
+      vec_tile<8, T, P, kBatchVecStrip, true>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
   } else {
     elem_tile<T, P>(s, f.dtype, f.rows, f.cols, f.base, t.i0, t.j0, out);
   }
@@ -679,8 +737,9 @@ __global__ __launch_bounds__(kThreads) void wb_diff2_batch_kernel(const DiffFiel
 }
 
 // Carry pass, stencil part: one tile per workgroup of one pass's fields.
+// Six waves a SIMD: at 80 VGPRs, two below what the compiler takes by itself.
 template <bool kIn, bool kLast>
-__global__ __launch_bounds__(kThreads) void wb_diff2_carry_kernel(const DiffField* __restrict__ fields,
+__global__ __launch_bounds__(kThreads, 6) void wb_diff2_carry_kernel(const DiffField* __restrict__ fields,
                                                                   const DiffTile* __restrict__ tiles, CarryTable in,
                                                                   CarryTable next, Sink<int64_t> sink) {
   __shared__ WgBuf ebuf, cbuf, pending;
@@ -807,9 +866,9 @@ struct TileGrid {
   __host__ __device__ int64_t per_strip() const { return (jend + jstep - 1) / jstep; }
 };
 __host__ __device__ inline TileGrid tile_grid(const DiffField& f) {
-  const int64_t nvec = f.cols / (f.dtype == WB_F32 ? 4 : 8);
+  const int64_t nvec = vec_count(f.cols, f.dtype == WB_F32 ? 4 : 8);
   if (f.kind == DIFF_FLAT) return {1, int64_t(kThreads) * kBatchFlatUnroll * kBatchFlatSub, nvec};
-  if (f.kind == DIFF_VEC) return {kBatchVecStrip, kThreads, nvec};
+  if (f.kind == DIFF_VEC || f.kind == DIFF_RAGGED) return {kBatchVecStrip, kThreads, nvec};
   return {kStrip, kThreads, f.cols};
 }
 
@@ -849,12 +908,16 @@ __global__ __launch_bounds__(kThreads) void wb_diff_tables_kernel(DiffField* fie
   tiles[i] = t;
 }
 
-// VEC and FLAT tiles need whole 16-byte vectors in every pass.
+// VEC and FLAT tiles need whole 16-byte vectors in every pass, RAGGED ones more
+// than one row of at least one vector: 8 fields of 4096 x 4098 bf16 took 390 us
+// a carry pass in ELEM tiles and 100 in RAGGED ones, 1695 and 170 as three held
+// passes. One-row fields stay ELEM (many columns, no rows to keep).
 int tile_kind(const void* const* src, int passes, int dtype, int64_t rows, int64_t cols) {
   const int V = dtype == WB_F32 ? 4 : 8;
-  if (cols % V != 0) return DIFF_ELEM;
+  const int other = rows > 1 && cols >= V ? DIFF_RAGGED : DIFF_ELEM;
+  if (cols % V != 0) return other;
   for (int c = 0; c < passes; ++c)
-    if (reinterpret_cast<uintptr_t>(src[c]) % 16 != 0) return DIFF_ELEM;
+    if (reinterpret_cast<uintptr_t>(src[c]) % 16 != 0) return other;
   return rows == 1 ? DIFF_FLAT : DIFF_VEC;
 }
 
@@ -890,7 +953,8 @@ int launch_diff2(const void* src, int dtype, int64_t rows, int64_t cols, int64_t
   const char* s = static_cast<const char*>(src);
   const bool f32 = dtype == WB_F32;
   const int V = f32 ? 4 : 8;
-  switch (tile_kind(&src, 1, dtype, rows, cols)) {
+  const int kind = tile_kind(&src, 1, dtype, rows, cols);
+  switch (kind) {
     case DIFF_FLAT: {
       const int64_t tiles = (cols / V + kThreads * kFlatUnroll - 1) / (kThreads * kFlatUnroll);
       const dim3 grid(static_cast<unsigned>(tiles < 65536 ? tiles : 65536));
@@ -900,12 +964,12 @@ int launch_diff2(const void* src, int dtype, int64_t rows, int64_t cols, int64_t
         hipLaunchKernelGGL(wb_diff2_flat_kernel<8>, grid, dim3(kThreads), 0, st, s, cols, out);
       break;
     }
-    case DIFF_VEC: {
-      const dim3 grid = strided_grid((cols / V + kThreads - 1) / kThreads, (rows + kVecStrip - 1) / kVecStrip);
-      if (f32)
-        hipLaunchKernelGGL(wb_diff2_vec_kernel<4>, grid, dim3(kThreads), 0, st, s, rows, cols, out);
-      else
-        hipLaunchKernelGGL(wb_diff2_vec_kernel<8>, grid, dim3(kThreads), 0, st, s, rows, cols, out);
+    case DIFF_VEC:
+    case DIFF_RAGGED: {
+      const dim3 grid = strided_grid((vec_count(cols, V) + kThreads - 1) / kThreads, (rows + kVecStrip - 1) / kVecStrip);
+      const auto kernel = kind == DIFF_VEC ? (f32 ? wb_diff2_vec_kernel<4, false> : wb_diff2_vec_kernel<8, false>)
+                                           : (f32 ? wb_diff2_vec_kernel<4, true> : wb_diff2_vec_kernel<8, true>);
+      hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, s, rows, cols, out);
       break;
     }
     default: {

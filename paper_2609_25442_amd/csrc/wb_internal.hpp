@@ -311,7 +311,7 @@ inline uint32_t qblock_workgroups(uint32_t n, uint32_t nfull, uint32_t npair) {
 // sum over k < passes of src[k][i * cols + j] << (16 k); its element 0 is
 // entry index base of the output. kind says how its tiles read it.
 constexpr int kMaxPasses = 3;
-enum DiffKind : uint8_t { DIFF_ELEM = 0, DIFF_VEC = 1, DIFF_FLAT = 2 };
+enum DiffKind : uint8_t { DIFF_ELEM = 0, DIFF_VEC = 1, DIFF_FLAT = 2, DIFF_RAGGED = 3 };
 struct DiffField {
   const void* src[kMaxPasses];
   int64_t rows, cols, base;
@@ -321,7 +321,7 @@ struct DiffField {
 };
 static_assert(sizeof(DiffField) == 56, "DiffField layout");
 // One workgroup's share: the tile of field `field` starting at row i0 and
-// column (ELEM) or 16-byte vector (VEC, FLAT) j0.
+// column (ELEM) or 16-byte vector (VEC, FLAT, RAGGED) j0.
 struct DiffTile {
   int32_t field, pad;
   int64_t i0, j0;

@@ -75,7 +75,7 @@ def _to_gpu(codes, dtype):
     return torch.from_numpy(codes.astype(np.float32)).cuda()
 
 
-# vector path (cols a multiple of 8 bf16 / 4 f32 values, aligned) and element path
+# rows of whole vectors (8 bf16 / 4 f32 values), ragged ones and ones below a vector
 SHAPES = [(1, 1), (1, 1000), (1000, 1), (3, 257), (130, 300), (65, 64), (64, 513), (200, 1), (2, 70000),
           (97, 2048), (33, 4104), (1, 300000), (1, 8), (1, 2056)]
 
@@ -227,6 +227,41 @@ def test_diff2_batch_capacity_overflow_reports_the_count():
     n, got = _batch(fields, 10)
     assert n == len(want)
     assert len(got) == 10 and all(want[i] == v for i, v in got.items())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("off", [0, 1, 3])
+def test_ragged_widths_at_any_address(dtype, off):
+    """Widths around one and two vectors, a wavefront's and a workgroup's, one
+    row and several, at any element address: the single-field stencil, a batch
+    and a carry pass give the oracle's entries."""
+    V = 8 if dtype == "bf16" else 4
+    rng = np.random.default_rng(off)
+    widths = [V - 1, V, V + 1, V + 2, V + 3, 2 * V - 1, 2 * V + 1, 64 * V - 1, 64 * V + 1, 65 * V + 2, 256 * V - 1,
+              256 * V + 1, 256 * V + V + 1]
+    fields_np, fields = [], []
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    for C in widths:
+        for R in (1, 3, 34):
+            F = rng.integers(0, 1 << 16, size=(R, C))
+            x = _to_gpu(np.concatenate([[7] * off, F.ravel(), [9]]), dtype)[off:off + R * C]
+            fields_np.append(([F], R, C))
+            fields.append((x, dtype, R, C))
+            want = nonzeros(diff2(F))
+            idx = torch.full((R * C,), -1, dtype=torch.int64, device="cuda")
+            val = torch.zeros(R * C, dtype=torch.int32, device="cuda")
+            say(f"[diff2 ragged] {dtype} +{off} {R}x{C}")
+            wb.diff2(x, dtype, R, C, idx, val, count)
+            n = int(count.item())
+            got = {(int(i) // C, int(i) % C): int(v) for i, v in zip(idx[:n].cpu().numpy(), val[:n].cpu().numpy())}
+            assert n == len(want) and got == want, (R, C)
+    want = _expected(fields_np)
+    count, got = _batch(fields, len(want) + 8)
+    assert count == len(want) and got == want
+    want, carried = _carry_expected(fields_np, 1)
+    numel = sum(R * C for _, R, C in fields_np)
+    n, c, got = _CarryRun(fields, numel, numel).run(fields, 0, True)
+    assert n == len(want[0]) and got == want[0]
 
 
 @pytest.mark.parametrize("n", [56, 57, 113])
