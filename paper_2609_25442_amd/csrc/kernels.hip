@@ -236,11 +236,36 @@ __device__ void run_bf16_f32(const Task& t, const char* src, char* dst, uint32_t
 }
 
 // Vectors at element alignment: gfx950 loads and stores global memory at any
-// byte address, so an unaligned vector costs the same instruction.
-typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
-typedef u32x2 u32x2_a1 __attribute__((aligned(1)));
-typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
-typedef uint32_t u32_a1 __attribute__((aligned(1)));
+// byte address, so an unaligned vector costs the same instruction. A pointer's
+// alignment does not survive template deduction (ld and st would promise the
+// plain type's), so the type is named here, and the address space with it: a
+// flat access would be split.
+template <typename T, int kAlign>
+struct Unaligned {
+  typedef T type __attribute__((aligned(kAlign)));
+  typedef __attribute__((address_space(1))) type* ptr;
+  typedef const __attribute__((address_space(1))) type* const_ptr;
+};
+
+template <typename T, int kAlign>
+__device__ __forceinline__ T ld_at(const char* p) {
+  const auto q = (typename Unaligned<T, kAlign>::const_ptr)(reinterpret_cast<uintptr_t>(p));
+#if WB_NT_LOAD
+  return __builtin_nontemporal_load(q);
+#else
+  return *q;
+#endif
+}
+
+template <typename T, int kAlign, typename P>
+__device__ __forceinline__ void st_at(T v, P* p) {
+  const auto q = (typename Unaligned<T, kAlign>::ptr)(reinterpret_cast<uintptr_t>(p));
+#if WB_NT_STORE
+  __builtin_nontemporal_store(v, q);
+#else
+  *q = v;
+#endif
+}
 
 // One chunk of a rectangle whose rows sit at any element address (flat shards
 // that start anywhere, odd widths): kSs, kDs the element bytes of both sides.
@@ -265,16 +290,16 @@ __device__ __forceinline__ void run_rows(const Task& t, const char* src, char* d
   const char* s = src + (uint64_t(r) * t.src_ld + off) * kSs;
   char* d = dr + off * kDs;
   if (kSs == 2 && kDs == 4) {
-    const u32x2 x = ld(reinterpret_cast<const u32x2_a2*>(s));
-    st(u32x4{x.x << 16, x.x & 0xFFFF0000u, x.y << 16, x.y & 0xFFFF0000u}, reinterpret_cast<u32x4_a2*>(d));
+    const u32x2 x = ld_at<u32x2, 2>(s);
+    st_at<u32x4, 2>(u32x4{x.x << 16, x.x & 0xFFFF0000u, x.y << 16, x.y & 0xFFFF0000u}, d);
     return;
   }
-  const u32x4 x = ld(reinterpret_cast<const u32x4_a2*>(s));
+  const u32x4 x = ld_at<u32x4, 2>(s);
   if (kSs == 4 && kDs == 2) {
     const f32x4 f = __builtin_bit_cast(f32x4, x);
-    st(u32x2{pack_bf16x2(f.x, f.y), pack_bf16x2(f.z, f.w)}, reinterpret_cast<u32x2_a2*>(d));
+    st_at<u32x2, 2>(u32x2{pack_bf16x2(f.x, f.y), pack_bf16x2(f.z, f.w)}, d);
   } else {
-    st(x, reinterpret_cast<u32x4_a2*>(d));
+    st_at<u32x4, 2>(x, d);
   }
 }
 
@@ -361,10 +386,10 @@ __device__ void run_transpose16(const Task& t, const char* src, char* dst, uint3
   u32x4 a[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
-    a[i] = ld(reinterpret_cast<const u32x4_a2*>(src + (uint64_t(r0 + i) * t.src_ld + c0) * 2));
+    a[i] = ld_at<u32x4, 2>(src + (uint64_t(r0 + i) * t.src_ld + c0) * 2);
 #pragma unroll
   for (int j = 0; j < 8; ++j)
-    st(column8(a, j), reinterpret_cast<u32x4_a2*>(dst + (uint64_t(c0 + j) * t.dst_ld + r0) * 2));
+    st_at<u32x4, 2>(column8(a, j), dst + (uint64_t(c0 + j) * t.dst_ld + r0) * 2);
 }
 
 // dst[c][r] = cvt(src[r][c]) with fp32 on at least one side, (32..128) rows x
@@ -380,9 +405,9 @@ __device__ __forceinline__ void run_transpose4(const Task& t, const char* src, c
   for (int i = 0; i < 4; ++i) {
     const char* p = src + (uint64_t(r0 + i) * t.src_ld + c0) * kSs;
     if (kSs == 4) {
-      a[i] = ld(reinterpret_cast<const u32x4_a2*>(p));
+      a[i] = ld_at<u32x4, 2>(p);
     } else {
-      const u32x2 x = ld(reinterpret_cast<const u32x2_a2*>(p));
+      const u32x2 x = ld_at<u32x2, 2>(p);
       a[i] = u32x4{x.x << 16, x.x & 0xFFFF0000u, x.y << 16, x.y & 0xFFFF0000u};
     }
   }
@@ -390,11 +415,11 @@ __device__ __forceinline__ void run_transpose4(const Task& t, const char* src, c
   for (int j = 0; j < 4; ++j) {
     char* p = dst + (uint64_t(c0 + j) * t.dst_ld + r0) * kDs;
     if (kDs == 4) {
-      st(u32x4{a[0][j], a[1][j], a[2][j], a[3][j]}, reinterpret_cast<u32x4_a2*>(p));
+      st_at<u32x4, 2>(u32x4{a[0][j], a[1][j], a[2][j], a[3][j]}, p);
     } else {
-      st(u32x2{pack_bf16x2(__uint_as_float(a[0][j]), __uint_as_float(a[1][j])),
-               pack_bf16x2(__uint_as_float(a[2][j]), __uint_as_float(a[3][j]))},
-         reinterpret_cast<u32x2_a2*>(p));
+      st_at<u32x2, 2>(u32x2{pack_bf16x2(__uint_as_float(a[0][j]), __uint_as_float(a[1][j])),
+                            pack_bf16x2(__uint_as_float(a[2][j]), __uint_as_float(a[3][j]))},
+                      p);
     }
   }
 }
@@ -911,7 +936,7 @@ __device__ __forceinline__ void qblock_wide(const QBlock& b, const BlockSource<k
     if (!on || r >= rows) continue;
     const char* p = whole ? S.template at<kF32>(recv, r, cg) : nullptr;
     if (p)
-      raw[k] = ld(reinterpret_cast<const u32x4_a2*>(p));
+      raw[k] = ld_at<u32x4, 2>(p);
     else
       odd = true;
   }
@@ -981,9 +1006,9 @@ __device__ __forceinline__ void qblock_wide(const QBlock& b, const BlockSource<k
         for (int m = 0; m < V; ++m)
           if (m < cols) dst[m] = static_cast<uint8_t>(w[m / 4] >> (8 * (m & 3)));
       } else if (kF32) {
-        st(w[0], reinterpret_cast<u32_a1*>(dst));
+        st_at<uint32_t, 1>(w[0], dst);
       } else {
-        st(u32x2{w[0], w[V / 4 - 1]}, reinterpret_cast<u32x2_a1*>(dst));
+        st_at<u32x2, 1>(u32x2{w[0], w[V / 4 - 1]}, dst);
       }
     }
   };
