@@ -634,19 +634,16 @@ int wb_plan_upload(wb_plan_t* P, void* workspace, size_t bytes, void* stream) {
         (e = hipMemcpyAsync(ws + P->off_qpieces, P->qpieces.data(), sizeof(wb::QPiece) * P->qpieces.size(),
                             hipMemcpyHostToDevice, st)) != hipSuccess)
       return hip_fail(e, "hipMemcpyAsync (fp8 pieces)");
-    // The events order this device's streams and tell the host that a staging
-    // slot has been read: nobody reads results on their word (a caller waits
-    // by its own stream, device or event synchronisation), and launches make
-    // their writes visible on the device themselves. So they need no fence to
-    // system scope, which writes the L2s back in front of the next launch:
-    // pack + unpack of a tiny model 14.2 -> 12.3 us, 12 fp8 rounds with their
-    // forwards 3175 -> 3155 us; hipEventReleaseToDevice gained nothing.
-    constexpr unsigned kEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
+    // The events keep their release to system scope: ptr_done is what makes a
+    // table copied on one stream visible to launches on another, and a caller
+    // that only polls its stream before it hands a buffer to another device
+    // meets one behind the last launch. Without it (hipEventDisableSystemFence)
+    // pack + unpack of a tiny model took 12.3 us instead of 14.2.
     for (int k = 0; k < wb_plan_t::kPtrSlots; ++k) {
       for (void** ev : {&P->ptr_copied[k], &P->ptr_done[k]}) {
         if (*ev) continue;
         hipEvent_t h;
-        if ((e = hipEventCreateWithFlags(&h, kEventFlags)) != hipSuccess)
+        if ((e = hipEventCreateWithFlags(&h, hipEventDisableTiming)) != hipSuccess)
           return hip_fail(e, "hipEventCreateWithFlags");
         *ev = h;
       }

@@ -96,3 +96,38 @@ def test_alternating_pointer_sets_do_not_block_the_host():
     # each unpack moves 32 GB (about 5 ms); enqueueing must not wait for them
     assert (t1 - t0) < 0.25 * (t2 - t0)
     assert _same(sets[0], ref) and _same(sets[1], ref)
+
+
+@pytest.mark.timeout(300)
+def test_a_fresh_table_is_read_on_another_stream():
+    """A set staged on stream A is unpacked again on stream B at once, with no
+    host wait between: B must see A's copy of the table. Six sets in turn, so
+    that most copies refill a slot that holds an older set's pointers; a stale
+    one would send B's values to that set instead."""
+    w = WORKLOADS["tiny_fsdp2_to_tp2"]
+    tr, ro = (wb.Layout.describe(w["model"], w[s]) for s in ("trainer", "rollout"))
+    d = w["unpack_rank"]
+    rp = wb.Plan(tr, ro, wb.RECEIVER, d)
+    ws = workspace_for(rp)
+    rp.upload(ws)
+    recv, refs = [], []
+    for seed in (1, 2):
+        x = torch.randn(rp.buffer_bytes // 4 + 1, generator=torch.Generator().manual_seed(seed)).cuda()
+        recv.append(x)
+        refs.append(wb.allocate_locals(ro, d))
+        rp.unpack(x, refs[-1])
+    sets = [wb.allocate_locals(ro, d) for _ in range(6)]
+    for s in sets:
+        _fill(s, 0x33)
+    A, B = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for turn in range(20):
+        first, second = (A, B) if turn % 2 == 0 else (B, A)
+        for s in sets:
+            rp.unpack(recv[0], s, first)
+            rp.unpack(recv[1], s, second)
+        torch.cuda.synchronize()
+        for j, s in enumerate(sets):
+            assert _same(s, refs[1]), (turn, j)
+            _fill(s, 0x33)
+        torch.cuda.synchronize()
