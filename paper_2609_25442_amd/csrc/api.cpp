@@ -924,6 +924,8 @@ int wb_diff2(const void* src, int32_t dtype, int64_t rows, int64_t cols, int64_t
 struct Diff2Tables {
   std::vector<wb::DiffField> fields;
   std::vector<int64_t> first{0};  // first tile of each field; the number of tiles last
+  bool strips = false;            // some field's tiles may be taken in strips
+  int passes = 0;                 // the most of any field
   int64_t ntiles() const { return first.back(); }
   size_t tiles_offset() const { return (fields.size() * sizeof(wb::DiffField) + 7) / 8 * 8; }
   size_t end() const { return tiles_offset() + ntiles() * sizeof(wb::DiffTile); }
@@ -967,6 +969,8 @@ static int diff2_batch_tables(const wb_field* fields, int32_t n, bool memory, Di
       }
     }
     T.first.push_back(T.ntiles() + wb::diff_tiles(f));
+    T.passes = std::max(T.passes, int(f.passes));
+    T.strips = T.strips || f.kind == wb::DIFF_VEC || f.kind == wb::DIFF_RAGGED;
     if (T.ntiles() > INT32_MAX) return set_error(WB_EINVAL, "more than 2^31 - 1 tiles");
     T.fields.push_back(f);
     base += numel;
@@ -1008,7 +1012,7 @@ int wb_diff2_batch(const wb_field* fields, int32_t n, void* workspace, size_t wo
     }
     const int e = wb::launch_diff2_batch(reinterpret_cast<const wb::DiffField*>(ws),
                                          reinterpret_cast<const wb::DiffTile*>(ws + T.tiles_offset()),
-                                         T.ntiles(), index, value, capacity,
+                                         T.ntiles(), T.strips, T.passes, index, value, capacity,
                                          reinterpret_cast<unsigned long long*>(count), stream);
     if (e != 0) return set_error(WB_EHIP, std::string("diff2 launch: ") + wb::hip_error_string(e));
     return WB_OK;
@@ -1020,7 +1024,7 @@ int wb_diff2_batch(const wb_field* fields, int32_t n, void* workspace, size_t wo
 // and reads the other), each `slots` slots of 16 bytes, slots the smallest
 // power of two at least twice the capacity (64 at least), then the staging
 // area of the stencil's carries (kCarryStage entries of 16 bytes per tile,
-// then a 4-byte count per tile).
+// then a count byte for each strip of a tile).
 struct CarryLayout {
   size_t counters = 0, table[2] = {0, 0}, stage = 0, stage_n = 0, bytes = 0;
   uint64_t slots = 0;
@@ -1106,7 +1110,7 @@ int wb_diff2_carry(const wb_field* fields, int32_t n, int32_t pass, int32_t last
     const wb::CarryTable& in = tab[(pass + 1) & 1];
     const int e = wb::launch_diff2_carry(reinterpret_cast<const wb::DiffField*>(ws), n,
                                          reinterpret_cast<const wb::DiffTile*>(ws + T.tiles_offset()),
-                                         T.ntiles(), pass > 0, last != 0, in, next, index, value,
+                                         T.ntiles(), T.strips, pass > 0, last != 0, in, next, index, value,
                                          capacity, reinterpret_cast<unsigned long long*>(count),
                                          reinterpret_cast<unsigned long long*>(carries), stream);
     if (e != 0) return set_error(WB_EHIP, std::string("diff2 carry launch: ") + wb::hip_error_string(e));

@@ -276,22 +276,43 @@ __device__ __forceinline__ void carry_spill(const CarryTable& t, bool spill, int
   if (spill) carry_insert(t, pos, packed);
 }
 
+// A workgroup's share of a launch's tile: all of it, or one of its kTileParts
+// strips.
+struct TileShare {
+  int64_t tile;
+  int part;
+  bool whole;
+};
+
+// The carries staged for a tile, from its four counts.
+__device__ __forceinline__ unsigned staged(uint32_t counts) {
+  return (counts & 0xFFu) + ((counts >> 8) & 0xFFu) + ((counts >> 16) & 0xFFu) + (counts >> 24);
+}
+
 // The workgroup's buffered carries. With kStage (a stencil tile) the first
-// kCarryStage are staged for the insert launch with plain stores and their
-// number stored for the tile (no atomic), the rest inserted and counted
-// here; otherwise all are inserted here and counted with one add.
+// kCarryStage (a strip: kCarryPart) are staged for the insert launch with
+// plain stores and their number stored for the tile (no atomic), the rest
+// inserted and counted here; otherwise all are inserted here and counted with
+// one add.
 template <bool kStage>
-__device__ __forceinline__ void carry_flush(WgBuf& b, const CarryTable& t) {
+__device__ __forceinline__ void carry_flush(WgBuf& b, const CarryTable& t, const TileShare& s) {
   __syncthreads();
   const unsigned n = b.n < unsigned(kWgCap) ? b.n : unsigned(kWgCap);
-  const unsigned m = kStage ? (n < unsigned(kCarryStage) ? n : unsigned(kCarryStage)) : 0u;
+  const unsigned room = kStage ? unsigned(s.whole ? kCarryStage : kCarryPart) : 0u, m = n < room ? n : room;
   if (threadIdx.x == 0) {
-    if (kStage) t.stage_n[blockIdx.x] = int32_t(m);
+    if (kStage) {
+      if (s.whole) {  // as the strips would count them: kCarryPart in each byte but the last
+        const unsigned full = 8 * (m / kCarryPart), all = kCarryPart * 0x01010101u;
+        t.stage_n[s.tile] = int32_t(full < 32 ? (all & ((1u << full) - 1u)) | (m % kCarryPart) << full : all);
+      } else {
+        reinterpret_cast<uint8_t*>(t.stage_n + s.tile)[s.part] = static_cast<uint8_t>(m);
+      }
+    }
     if (n > m) atomicAdd(t.count + blockIdx.x % kCarryCounters, static_cast<unsigned long long>(n - m));
   }
   for (unsigned k = threadIdx.x; k < n; k += blockDim.x) {
     if (k < m) {
-      int64_t* e = t.stage + 2 * (int64_t(blockIdx.x) * kCarryStage + k);
+      int64_t* e = t.stage + 2 * (s.tile * kCarryStage + s.part * kCarryPart + k);
       e[0] = b.pos[k];
       e[1] = b.val[k];
     } else {
@@ -313,6 +334,7 @@ struct CarryOut {
   Sink<int64_t> sink;
   CarryTable in, next;
   int64_t field;
+  TileShare share;
   __device__ __forceinline__ void split(bool c, int64_t pos, int s, int64_t f, int lane) const {
     if (kLast) {
       sink_append(*ebuf, sink, c && s != 0, pos, int64_t(s), lane);
@@ -373,7 +395,7 @@ struct CarryOut {
   // the emitted values and the carries of the workgroup
   __device__ __forceinline__ void flush_outputs() const {
     sink_flush(*ebuf, sink);
-    if (!kLast) carry_flush<kStage>(*cbuf, next);
+    if (!kLast) carry_flush<kStage>(*cbuf, next, share);
   }
   __device__ __forceinline__ void flush() const {
     __syncthreads();
@@ -492,8 +514,8 @@ __device__ __forceinline__ void load_row_vec(const Passes<P>& s, int64_t rowoff,
   }
 }
 
-// VEC tile: thread t takes the V columns of vector vb + t over rows [i0, i0 +
-// S), after two halo rows, one row of state per lane. The two columns left of
+// VEC tile: thread t takes the V columns of vector vb + t over rows [i0, i1),
+// after two halo rows, one row of state per lane. The two columns left of
 // a lane's vector are the previous lane's last two (the first lane of each
 // wavefront loads them). The next row's vectors of every pass (and, for the
 // first lane, the two values left of them) are loaded before the current row
@@ -508,15 +530,14 @@ __device__ __forceinline__ void load_row_vec(const Passes<P>& s, int64_t rowoff,
 // vector of a row is moved left inside it, and its lane loads the values left
 // of it as well. A kind of its own because the aligned rows lose with its code
 // (f32, 2.8 GB a pass: 750 -> 870 us).
-template <int V, typename T, int P, int S, bool kRagged, class Out>
-__device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t rows, int64_t cols, int64_t base, int64_t i0,
+template <int V, typename T, int P, bool kRagged, class Out>
+__device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t cols, int64_t base, int64_t i0, int64_t i1,
                                          int64_t vb, const Out& out) {
   const int lane = threadIdx.x & 63;
   const int64_t v = vb + threadIdx.x;
   const bool live = v < vec_count(cols, V);
   int skip = 0;
   const int64_t j0 = kRagged ? vec_at(v, cols, V, skip) : v * V;
-  const int64_t i1 = i0 + S < rows ? i0 + S : rows;
   const int64_t rb = cols * (16 / V);
   const bool apart = lane == 0 || skip != 0, left = apart && j0 >= 1;
   T ha[V], hb[V];  // h of the last two rows
@@ -663,7 +684,7 @@ __global__ __launch_bounds__(kThreads) void wb_diff2_vec_kernel(const char* __re
   const int64_t nvec = vec_count(cols, V);
   for (int64_t vb = int64_t(blockIdx.x) * kThreads; vb < nvec; vb += int64_t(gridDim.x) * kThreads)
     for (int64_t i0 = int64_t(blockIdx.y) * kVecStrip; i0 < rows; i0 += int64_t(gridDim.y) * kVecStrip)
-      vec_tile<V, int, 1, kVecStrip, kRagged>(s, rows, cols, 0, i0, vb, out);
+      vec_tile<V, int, 1, kRagged>(s, cols, 0, i0, i0 + kVecStrip < rows ? i0 + kVecStrip : rows, vb, out);
   out.flush();
 }
 
@@ -682,25 +703,44 @@ __global__ __launch_bounds__(kThreads) void wb_diff2_flat_kernel(const char* __r
   out.flush();
 }
 
-// Batched launches: workgroup b takes tile b of the table, VEC tiles (vec_tile)
-// of kBatchVecStrip rows and FLAT tiles of several sub-tiles (fewer, larger
-// table rows). Held passes recombine up to kMaxPasses passes in int64; carry
-// passes read one pass in int. Bound: HBM reads in flight; a TP2 rank of an
-// 8-layer 8 B model (2.8 GB of bf16 a pass) in strips of 128 rows 574, 557
-// with vec_tile's pairs of rows; of 64, 32 and 16 rows 546, 519 and 535 us
-// (5.4 TB/s): shorter strips even out the launch's end until the two halo rows
-// cost more. With non-temporal loads 620, with the XCD-aware order of the copy
-// launches 531, with registers for two more waves a SIMD (spills) 780.
-constexpr int kBatchVecStrip = 32;
+// Batched launches: a tile of the table is kBatchVecTile rows of a VEC or RAGGED
+// field or several sub-tiles of a FLAT one (fewer, larger table rows), and its
+// VEC and RAGGED tiles are taken in kTileParts strips by as many workgroups:
+// the table, the carries staged per tile and the launches that walk them keep
+// the size of the tall tiles. Held passes recombine up to kMaxPasses passes in
+// int64; carry passes read one pass in int. Bound: HBM reads in flight; a TP2
+// rank of an 8-layer 8 B model (2.8 GB of bf16 a pass) in strips of 128 rows
+// 574, 557 with vec_tile's pairs of rows; of 64, 32 and 16 rows 546, 519 and
+// 535 us (5.4 TB/s): shorter strips even out the launch's end until the two
+// halo rows cost more. With non-temporal loads 620, with the XCD-aware order of
+// the copy launches 531, with registers for two more waves a SIMD (spills) 780.
+constexpr int kBatchVecTile = 128;
+constexpr int kBatchVecStrip = kBatchVecTile / kTileParts;
 constexpr int kBatchFlatUnroll = 4;
 constexpr int kBatchFlatSub = 8;  // sub-tiles of kBatchFlatUnroll x kThreads vectors per FLAT tile
 
+// How a field is cut into tiles: strips of istep rows, each cut at multiples
+// of jstep columns (ELEM) or 16-byte vectors (VEC, FLAT, RAGGED) below jend.
+struct TileGrid {
+  int64_t istep, jstep, jend;
+  __host__ __device__ int64_t per_strip() const { return (jend + jstep - 1) / jstep; }
+};
+__host__ __device__ inline TileGrid tile_grid(const DiffField& f) {
+  const int64_t nvec = vec_count(f.cols, f.dtype == WB_F32 ? 4 : 8);
+  if (f.kind == DIFF_FLAT) return {1, int64_t(kThreads) * kBatchFlatUnroll * kBatchFlatSub, nvec};
+  if (f.kind == DIFF_VEC || f.kind == DIFF_RAGGED) return {kBatchVecTile, kThreads, nvec};
+  return {kStrip, kThreads, f.cols};
+}
+
 template <typename T, int P, class Out>
-__device__ __forceinline__ void batch_tile(const DiffField& f, const DiffTile& t, const Out& out) {
+__device__ __forceinline__ void batch_tile(const DiffField& f, const DiffTile& t, const TileShare& share,
+                                           const Out& out) {
   Passes<P> s;
 #pragma unroll
   for (int c = 0; c < P; ++c) s.p[c] = global_ptr(f.src[c]);
   s.n = P == 1 ? 1 : f.passes;
+  const int64_t i0 = t.i0 + share.part * kBatchVecStrip;
+  const int64_t end = i0 + (share.whole ? kBatchVecTile : kBatchVecStrip), i1 = end < f.rows ? end : f.rows;
   if (f.kind == DIFF_FLAT) {
     for (int q = 0; q < kBatchFlatSub; ++q) {
       const int64_t cb = t.j0 + int64_t(q) * kBatchFlatUnroll * kThreads;
@@ -710,46 +750,72 @@ __device__ __forceinline__ void batch_tile(const DiffField& f, const DiffTile& t
         flat_tile<8, T, P, kBatchFlatUnroll>(s, f.cols, f.base, cb, out);
     }
   } else if (f.kind == DIFF_VEC) {
+    if (i0 >= i1) return;  // no row of the strip (uniform over the workgroup)
     if (f.dtype == WB_F32)
-      vec_tile<4, T, P, kBatchVecStrip, false>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
+      vec_tile<4, T, P, false>(s, f.cols, f.base, i0, i1, t.j0, out);
     else
-      vec_tile<8, T, P, kBatchVecStrip, false>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
+      vec_tile<8, T, P, false>(s, f.cols, f.base, i0, i1, t.j0, out);
   } else if (f.kind == DIFF_RAGGED) {
+    if (i0 >= i1) return;  // no row of the strip (uniform over the workgroup)
     if (f.dtype == WB_F32)
-      vec_tile<4, T, P, kBatchVecStrip, true>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
+      vec_tile<4, T, P, true>(s, f.cols, f.base, i0, i1, t.j0, out);
     else
-      vec_tile<8, T, P, kBatchVecStrip, true>(s, f.rows, f.cols, f.base, t.i0, t.j0, out);
+      vec_tile<8, T, P, true>(s, f.cols, f.base, i0, i1, t.j0, out);
   } else {
     elem_tile<T, P>(s, f.dtype, f.rows, f.cols, f.base, t.i0, t.j0, out);
   }
 }
 
+// The share of workgroup b of a launch, and its tile t. With kCut a tile has
+// kTileParts workgroups: one that is not cut into strips is its first one's
+// alone; the others go strip by strip across the field's columns, so that
+// neighbouring workgroups read on along the rows (tile by tile, the fp32 passes
+// took 5-8 % longer).
+template <bool kCut>
+__device__ __forceinline__ TileShare tile_share(const DiffField* __restrict__ fields,
+                                                const DiffTile* __restrict__ tiles, unsigned b, DiffTile& t) {
+  const unsigned k = kCut ? b / kTileParts : b;
+  t = tiles[k];
+  if (!kCut) return {int64_t(k), 0, true};
+  const DiffField& f = fields[t.field];
+  if (f.kind != DIFF_VEC && f.kind != DIFF_RAGGED) return {int64_t(k), int(b % kTileParts), true};
+  const unsigned per = unsigned(tile_grid(f).per_strip()), first = k - unsigned(t.j0) / kThreads;
+  const unsigned r = b - first * kTileParts, part = r / per, col = r - part * per;
+  t.j0 = int64_t(col) * kThreads;
+  return {int64_t(first + col), int(part), false};
+}
+
+template <bool kCut>
 __global__ __launch_bounds__(kThreads) void wb_diff2_batch_kernel(const DiffField* __restrict__ fields,
                                                                   const DiffTile* __restrict__ tiles,
                                                                   Sink<int64_t> sink) {
+  DiffTile t;
+  const TileShare share = tile_share<kCut>(fields, tiles, blockIdx.x, t);
+  if (share.whole && share.part) return;
   __shared__ WgBuf buf;
   wg_init(buf);
   __syncthreads();
   const ListOut<int64_t> out{&buf, sink};
-  const DiffTile t = tiles[blockIdx.x];
-  batch_tile<int64_t, kMaxPasses>(fields[t.field], t, out);
+  batch_tile<int64_t, kMaxPasses>(fields[t.field], t, share, out);
   out.flush();
 }
 
 // Carry pass, stencil part: one tile per workgroup of one pass's fields.
 // Six waves a SIMD: at 80 VGPRs, two below what the compiler takes by itself.
-template <bool kIn, bool kLast>
+template <bool kIn, bool kLast, bool kCut>
 __global__ __launch_bounds__(kThreads, 6) void wb_diff2_carry_kernel(const DiffField* __restrict__ fields,
-                                                                  const DiffTile* __restrict__ tiles, CarryTable in,
-                                                                  CarryTable next, Sink<int64_t> sink) {
+                                                                     const DiffTile* __restrict__ tiles, CarryTable in,
+                                                                     CarryTable next, Sink<int64_t> sink) {
+  DiffTile t;
+  const TileShare share = tile_share<kCut>(fields, tiles, blockIdx.x, t);
+  if (share.whole && share.part) return;
   __shared__ WgBuf ebuf, cbuf, pending;
   wg_init(ebuf);
   wg_init(cbuf);
   wg_init(pending);
   __syncthreads();
-  const DiffTile t = tiles[blockIdx.x];
-  const CarryOut<kIn, kLast, true> out{&ebuf, &cbuf, &pending, sink, in, next, int64_t(t.field)};
-  batch_tile<int, 1>(fields[t.field], t, out);
+  const CarryOut<kIn, kLast, true> out{&ebuf, &cbuf, &pending, sink, in, next, int64_t(t.field), share};
+  batch_tile<int, 1>(fields[t.field], t, share, out);
   out.flush();
 }
 
@@ -783,7 +849,7 @@ __global__ __launch_bounds__(kThreads) void wb_carry_rest_kernel(const DiffField
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int64_t slots = static_cast<int64_t>(in.mask) + 1;
-  const CarryOut<false, kLast, false> out{&ebuf, &cbuf, nullptr, sink, in, next, 0};
+  const CarryOut<false, kLast, false> out{&ebuf, &cbuf, nullptr, sink, in, next, 0, {0, 0, true}};
   for (int64_t b0 = int64_t(blockIdx.x) * kThreads; b0 < slots; b0 += int64_t(gridDim.x) * kThreads) {
     const int64_t h = b0 + threadIdx.x;
     int64_t pos = 0, field = 0;
@@ -811,11 +877,12 @@ __global__ __launch_bounds__(kThreads) void wb_carry_rest_kernel(const DiffField
 // Insert the carries the stencil workgroups staged: one thread per staging
 // slot of every tile.
 __global__ __launch_bounds__(kThreads) void wb_carry_insert_kernel(CarryTable next, int64_t ntiles) {
-  const int64_t total = ntiles * kCarryStage;
-  const int64_t stride = int64_t(gridDim.x) * kThreads;
-  for (int64_t e = int64_t(blockIdx.x) * kThreads + threadIdx.x; e < total; e += stride) {
-    const int64_t t = e / kCarryStage, k = e - t * kCarryStage;
-    if (k < next.stage_n[t]) carry_insert(next, next.stage[2 * e], next.stage[2 * e + 1]);
+  const uint64_t total = uint64_t(ntiles) * kCarryStage;
+  const uint64_t stride = uint64_t(gridDim.x) * kThreads;
+  for (uint64_t e = uint64_t(blockIdx.x) * kThreads + threadIdx.x; e < total; e += stride) {
+    const unsigned k = unsigned(e % kCarryStage);
+    const uint32_t n = (static_cast<uint32_t>(next.stage_n[e / kCarryStage]) >> (8 * (k / kCarryPart))) & 0xFFu;
+    if (k % kCarryPart < n) carry_insert(next, next.stage[2 * e], next.stage[2 * e + 1]);
   }
 }
 
@@ -840,7 +907,7 @@ __global__ __launch_bounds__(kThreads) void wb_carry_report_kernel(const int32_t
                                                                   int64_t capacity, unsigned long long* out) {
   __shared__ unsigned long long part[kThreads];
   unsigned long long n = 0;
-  for (int64_t t = threadIdx.x; t < ntiles; t += kThreads) n += static_cast<unsigned long long>(stage_n[t]);
+  for (int64_t t = threadIdx.x; t < ntiles; t += kThreads) n += staged(static_cast<uint32_t>(stage_n[t]));
   if (threadIdx.x < kCarryCounters) n += counters[threadIdx.x];
   part[threadIdx.x] = n;
   __syncthreads();
@@ -858,19 +925,6 @@ __global__ __launch_bounds__(kThreads) void wb_carry_report_kernel(const int32_t
 
 
 __global__ void wb_zero_count_kernel(unsigned long long* count) { *count = 0; }
-
-// How a field is cut into tiles: strips of istep rows, each cut at multiples
-// of jstep columns (ELEM) or 16-byte vectors (VEC, FLAT) below jend.
-struct TileGrid {
-  int64_t istep, jstep, jend;
-  __host__ __device__ int64_t per_strip() const { return (jend + jstep - 1) / jstep; }
-};
-__host__ __device__ inline TileGrid tile_grid(const DiffField& f) {
-  const int64_t nvec = vec_count(f.cols, f.dtype == WB_F32 ? 4 : 8);
-  if (f.kind == DIFF_FLAT) return {1, int64_t(kThreads) * kBatchFlatUnroll * kBatchFlatSub, nvec};
-  if (f.kind == DIFF_VEC || f.kind == DIFF_RAGGED) return {kBatchVecStrip, kThreads, nvec};
-  return {kStrip, kThreads, f.cols};
-}
 
 // The field and tile tables of a batched launch, written on the device from
 // up to kTableFields fields in the kernel arguments (below their 4 KiB): one
@@ -1007,19 +1061,33 @@ int launch_diff_tables(const DiffField* fields, const int64_t* first, int32_t n,
   return hipSuccess;
 }
 
-int launch_diff2_batch(const DiffField* fields, const DiffTile* tiles, int64_t ntiles, int64_t* index, int64_t* value,
-                       int64_t capacity, unsigned long long* count, void* stream) {
+// Whether a launch takes its VEC and RAGGED tiles in strips: as long as its
+// threads stay below the 2^32 of a grid.
+static bool cut_tiles(bool strips, int64_t ntiles) {
+  return strips && ntiles * kTileParts * kThreads < (int64_t(1) << 32);
+}
+
+constexpr int64_t kWholeTiles = 4096;
+
+int launch_diff2_batch(const DiffField* fields, const DiffTile* tiles, int64_t ntiles, bool strips, int passes,
+                       int64_t* index, int64_t* value, int64_t capacity, unsigned long long* count, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipLaunchKernelGGL(wb_zero_count_kernel, dim3(1), dim3(1), 0, st, count);
   if (ntiles == 0) return hipGetLastError();
   const Sink<int64_t> out{index, value, capacity, count};
-  hipLaunchKernelGGL(wb_diff2_batch_kernel, dim3(static_cast<unsigned>(ntiles)), dim3(kThreads), 0, st, fields, tiles,
-                     out);
+  // one held pass takes its tiles whole once there are a few times as many as
+  // workgroups fit the chip: its int64 arithmetic bounds it, that of the halo
+  // rows too (7 GB of bf16 3570 us in strips, 3320 whole; 1.7 GB 470 and 483).
+  // Two passes take strips at every size (28 GB of fp32 9.4 and 10.0 ms).
+  const bool cut = cut_tiles(strips, ntiles) && (passes > 1 || ntiles < kWholeTiles);
+  const dim3 grid(static_cast<unsigned>(cut ? ntiles * kTileParts : ntiles));
+  const auto kernel = cut ? wb_diff2_batch_kernel<true> : wb_diff2_batch_kernel<false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, fields, tiles, out);
   return hipGetLastError();
 }
 
-int launch_diff2_carry(const DiffField* fields, int32_t nfields, const DiffTile* tiles, int64_t ntiles, bool has_in,
-                       bool last, const CarryTable& in, const CarryTable& next, int64_t* index, int64_t* value,
+int launch_diff2_carry(const DiffField* fields, int32_t nfields, const DiffTile* tiles, int64_t ntiles, bool strips,
+                       bool has_in, bool last, const CarryTable& in, const CarryTable& next, int64_t* index, int64_t* value,
                        int64_t capacity, unsigned long long* count, unsigned long long* carries, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t slots = last ? 0 : static_cast<int64_t>(next.mask) + 1;
@@ -1028,18 +1096,13 @@ int launch_diff2_carry(const DiffField* fields, int32_t nfields, const DiffTile*
                      dim3(kThreads), 0, st, next.slot, slots, next.count, count);
   const Sink<int64_t> sink{index, value, capacity, count};
   if (ntiles > 0) {
-    const dim3 grid(static_cast<unsigned>(ntiles));
-    if (has_in && last)
-      hipLaunchKernelGGL((wb_diff2_carry_kernel<true, true>), grid, dim3(kThreads), 0, st, fields, tiles, in, next, sink);
-    else if (has_in)
-      hipLaunchKernelGGL((wb_diff2_carry_kernel<true, false>), grid, dim3(kThreads), 0, st, fields, tiles, in, next,
-                         sink);
-    else if (last)
-      hipLaunchKernelGGL((wb_diff2_carry_kernel<false, true>), grid, dim3(kThreads), 0, st, fields, tiles, in, next,
-                         sink);
-    else
-      hipLaunchKernelGGL((wb_diff2_carry_kernel<false, false>), grid, dim3(kThreads), 0, st, fields, tiles, in, next,
-                         sink);
+    const bool cut = cut_tiles(strips, ntiles);
+    const dim3 grid(static_cast<unsigned>(cut ? ntiles * kTileParts : ntiles));
+    const auto kernel = has_in && last ? (cut ? wb_diff2_carry_kernel<true, true, true> : wb_diff2_carry_kernel<true, true, false>)
+                        : has_in       ? (cut ? wb_diff2_carry_kernel<true, false, true> : wb_diff2_carry_kernel<true, false, false>)
+                        : last         ? (cut ? wb_diff2_carry_kernel<false, true, true> : wb_diff2_carry_kernel<false, true, false>)
+                                       : (cut ? wb_diff2_carry_kernel<false, false, true> : wb_diff2_carry_kernel<false, false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, fields, tiles, in, next, sink);
   }
   if (ntiles > 0 && !last) {
     const int64_t want = (ntiles * kCarryStage + kThreads - 1) / kThreads;

@@ -332,12 +332,15 @@ static_assert(sizeof(DiffTile) == 24, "DiffTile layout");
 // field << 32 | carry as uint32; `count` points to kCarryCounters counters
 // whose sum is the number of carries inserted, then a flag set when an
 // insert found no free slot within kCarryProbes of its hash. The stencil
-// workgroup of tile t stages up to kCarryStage of its carries at
-// stage[2 * (t * kCarryStage + k)] (position, packed carry) and their number
-// at stage_n[t]; a later launch inserts them.
+// stages up to kCarryStage of the carries of tile t at
+// stage[2 * (t * kCarryStage + k)] (position, packed carry), kCarryPart for
+// each of the kTileParts strips a tile may be cut into, and their numbers in
+// the bytes of stage_n[t]; a later launch inserts them.
 constexpr int kCarryCounters = 64;
 constexpr int kCarryProbes = 256;
 constexpr int kCarryStage = 64;
+constexpr int kTileParts = 4, kCarryPart = kCarryStage / kTileParts;
+static_assert(kTileParts == sizeof(int32_t) && kCarryPart <= 255, "a byte of a tile's counts per strip");
 struct CarryTable {
   int64_t* slot;
   unsigned long long* count;
@@ -449,12 +452,13 @@ int64_t diff_tiles(DiffField& f);
 // free on return
 int launch_diff_tables(const DiffField* fields, const int64_t* first, int32_t n, DiffField* dev_fields,
                        DiffTile* dev_tiles, void* stream);
-int launch_diff2_batch(const DiffField* fields, const DiffTile* tiles, int64_t ntiles, int64_t* index, int64_t* value,
-                       int64_t capacity, unsigned long long* count, void* stream);
+// strips: some field is VEC or RAGGED; passes: the most of any field
+int launch_diff2_batch(const DiffField* fields, const DiffTile* tiles, int64_t ntiles, bool strips, int passes,
+                       int64_t* index, int64_t* value, int64_t capacity, unsigned long long* count, void* stream);
 // one carry pass: clears `next` (unless last), runs the stencil over the
 // tiles, then (has_in) the carries of `in` at positions the stencil skipped,
 // and copies next's carry count to *carries
-int launch_diff2_carry(const DiffField* fields, int32_t nfields, const DiffTile* tiles, int64_t ntiles, bool has_in,
-                       bool last, const CarryTable& in, const CarryTable& next, int64_t* index, int64_t* value,
+int launch_diff2_carry(const DiffField* fields, int32_t nfields, const DiffTile* tiles, int64_t ntiles, bool strips,
+                       bool has_in, bool last, const CarryTable& in, const CarryTable& next, int64_t* index, int64_t* value,
                        int64_t capacity, unsigned long long* count, unsigned long long* carries, void* stream);
 }  // namespace wb

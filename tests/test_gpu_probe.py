@@ -267,11 +267,12 @@ def test_ragged_widths_at_any_address(dtype, off):
 @pytest.mark.parametrize("n", [56, 57, 113])
 def test_tables_of_many_fields(n):
     """The field and tile tables are written 56 fields a launch: fields on both
-    sides of each cut, empty ones among them, and heights around a pair of rows
-    and a strip, in one batch of held passes and as carried passes, equal the
+    sides of each cut, empty ones among them, and heights around a pair of
+    rows, a strip (32 rows) and a tile (128), in one batch of held passes and as carried passes, equal the
     oracle's entries."""
     rng = np.random.default_rng(n)
-    shapes = [(1, 16), (2, 16), (3, 24), (5, 13), (0, 8), (127, 8), (128, 8), (129, 16), (130, 8), (131, 7), (1, 999)]
+    shapes = [(1, 16), (2, 16), (3, 24), (5, 13), (0, 8), (127, 8), (128, 8), (129, 16), (130, 8), (131, 7), (1, 999),
+              (31, 16), (32, 9), (33, 16), (34, 11), (63, 8), (64, 17), (65, 8), (66, 15), (97, 24), (257, 9)]
     fields_np = []
     for k in range(n):
         R, C = shapes[(k + n) % len(shapes)]
@@ -290,6 +291,45 @@ def test_tables_of_many_fields(n):
         say(f"[diff2 tables] carry pass {k} of {n} fields")
         count, c, got = runner.run(one, k, k == 1)
         assert (count, c) == (len(want[k]), carried[k]) and got == want[k]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_more_tiles_than_a_grid_holds_strips(dtype):
+    """A field 8 (4) columns wide of 2^22 tiles and a few rows more: strips of its
+    tiles would be more workgroups than a launch takes, so each tile is one.
+    Zero but for a few elements, whose entries are known."""
+    V = 8 if dtype == "bf16" else 4
+    R = (1 << 29) + 5
+    x = torch.zeros(R * V, dtype=TORCH[dtype], device="cuda")
+    at = [(1, 2), (127, V - 1), (128, 0), (1 << 20, 1), (R - 130, 3), (R - 1, 0)]
+    want = {}
+    for k, (i, j) in enumerate(at):
+        v = 65535 - k
+        x[i * V + j:i * V + j + 1] = _to_gpu(np.array([v]), dtype)
+        for a in range(3):
+            for b in range(3):
+                if i + a < R and j + b < V:
+                    p = (i + a) * V + j + b
+                    want[p] = want.get(p, 0) + v * (1, -2, 1)[a] * (1, -2, 1)[b]
+    want = {p: v for p, v in want.items() if v}
+    fields = [(x, dtype, R, V)]
+    say(f"[diff2] {dtype} {R}x{V}: held")
+    idx, val, count = (torch.zeros(n, dtype=torch.int64, device="cuda") for n in (256, 256, 2))
+    ws = torch.empty(wb.diff2_batch_workspace(fields), dtype=torch.uint8, device="cuda")
+    wb.diff2_batch(fields, idx, val, count[:1], ws)
+    n = int(count[0].item())
+    assert n == len(want) and dict(zip(idx[:n].tolist(), val[:n].tolist())) == want
+    del ws
+    say("[diff2] carried")
+    ws = torch.empty(wb.diff2_carry_workspace(fields, 64), dtype=torch.uint8, device="cuda")
+    wb.diff2_carry(fields, 0, False, 64, idx, val, count[:1], count[1:], ws)
+    n, c = count.tolist()
+    assert dict(zip(idx[:n].tolist(), val[:n].tolist())) == {p: v & 0xFFFF for p, v in want.items() if v & 0xFFFF}
+    assert c == sum(v >> 16 != 0 for v in want.values())
+    x.zero_()
+    wb.diff2_carry(fields, 1, True, 64, idx, val, count[:1], count[1:], ws)
+    n = int(count[0].item())
+    assert dict(zip(idx[:n].tolist(), val[:n].tolist())) == {p: v >> 16 for p, v in want.items() if v >> 16}
 
 
 def _carry_fields(rng, kind, passes):

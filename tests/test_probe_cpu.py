@@ -199,6 +199,20 @@ def test_diff2_carry_workspace():
         ws([([A, A + 64], "bf16", 4, 4)], 10)       # a carry pass reads one pass per field
 
 
+@pytest.mark.parametrize("dtype,rows,cols,off,tiles", [
+    ("bf16", 128, 2048, 0, 1), ("bf16", 129, 2048, 0, 2), ("bf16", 4096, 4096, 0, 32 * 2), ("bf16", 1 << 20, 8, 0, 8192),
+    ("f32", 128, 1024, 0, 1), ("f32", 4096, 4096, 0, 32 * 4), ("bf16", 4096, 4098, 0, 32 * 3), ("f32", 256, 1027, 4, 4),
+    ("bf16", 1, 1 << 20, 0, 16), ("bf16", 65, 7, 0, 2)])
+def test_tables_and_staging_by_tall_tiles(dtype, rows, cols, off, tiles):
+    """A table row and 64 staged carries per 128 rows x 256 vectors, whatever
+    strips the launches cut them into: a probe's workspace is below 1 % of the
+    data of wide fields."""
+    f = [((1 << 20) + off, dtype, rows, cols)]
+    assert wb.diff2_batch_workspace(f) == 56 + 24 * tiles
+    head, slots = -(-(56 + 24 * tiles) // 256) * 256, 64
+    assert wb.diff2_carry_workspace(f, 1) == head + 2048 + 2 * slots * 16 + tiles * 64 * 16 + -(-tiles * 4 // 256) * 256
+
+
 def test_diff2_carry_argument_checks():
     """Refusals decided on the host before any device access."""
     A = 1 << 20
