@@ -523,16 +523,20 @@ __device__ __forceinline__ void load_row_vec(const Passes<P>& s, int64_t rowoff,
 // rows loaded and then computed: carry passes (one pass, int) 5-7 % faster
 // per pass than one row and faster than two or four rows; held passes (three,
 // int64) 9.56 -> 8.05 ms for 48 GB; two rows ahead gave nothing more.
-// A lane's differences are tested by one OR, and rows go in pairs so that
-// loads and the last two rows' h change places instead of being moved: the
-// arithmetic per element bounded the passes before HBM did.
+// A lane's differences are tested by one OR, and (kPairs) rows go in pairs so
+// that loads and the last two rows' h change places instead of being moved: the
+// arithmetic per element bounded the passes before HBM did. Single-field
+// launches of aligned fp32 rows take them one by one (0.05 to 4 GB: pairs 2-5 %
+// slower, 2.1 GB 400 and 387 us); of bf16 rows, whose single steps were as often
+// faster as slower (0.26 GB 63 us in pairs and 57, 1.05 GB 206 and 218), in pairs.
 // kRagged: any width of at least a vector and any element address; the last
 // vector of a row is moved left inside it, and its lane loads the values left
 // of it as well. A kind of its own because the aligned rows lose with its code
 // (f32, 2.8 GB a pass: 750 -> 870 us).
-template <int V, typename T, int P, bool kRagged, class Out>
+template <int V, typename T, int P, bool kRagged, bool kPairs, class Out>
 __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t cols, int64_t base, int64_t i0, int64_t i1,
                                          int64_t vb, const Out& out) {
+  static_assert(kPairs || !kRagged, "ragged rows go in pairs");
   const int lane = threadIdx.x & 63;
   const int64_t v = vb + threadIdx.x;
   const bool live = v < vec_count(cols, V);
@@ -606,6 +610,24 @@ __device__ __forceinline__ void vec_tile(const Passes<P>& s, int64_t cols, int64
   uint4 qa[P], qb[P];
   uint2 la[P], lb[P];
   fetch(ist, qa, la);
+  if (!kPairs) {
+    for (int64_t i = ist; i < i1; ++i) {
+      fetch(i + 1, qb, lb);
+      row(i, qa, la, ha, hb);
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        const T h = hb[k];
+        hb[k] = ha[k];
+        ha[k] = h;
+      }
+#pragma unroll
+      for (int c = 0; c < P; ++c) {
+        qa[c] = qb[c];
+        la[c] = lb[c];
+      }
+    }
+    return;
+  }
   for (int64_t i = ist; i < i1; i += 2) {
     fetch(i + 1, qb, lb);
     row(i, qa, la, hb, ha);
@@ -684,7 +706,7 @@ __global__ __launch_bounds__(kThreads) void wb_diff2_vec_kernel(const char* __re
   const int64_t nvec = vec_count(cols, V);
   for (int64_t vb = int64_t(blockIdx.x) * kThreads; vb < nvec; vb += int64_t(gridDim.x) * kThreads)
     for (int64_t i0 = int64_t(blockIdx.y) * kVecStrip; i0 < rows; i0 += int64_t(gridDim.y) * kVecStrip)
-      vec_tile<V, int, 1, kRagged>(s, cols, 0, i0, i0 + kVecStrip < rows ? i0 + kVecStrip : rows, vb, out);
+      vec_tile<V, int, 1, kRagged, kRagged || V == 8>(s, cols, 0, i0, i0 + kVecStrip < rows ? i0 + kVecStrip : rows, vb, out);
   out.flush();
 }
 
@@ -752,15 +774,15 @@ __device__ __forceinline__ void batch_tile(const DiffField& f, const DiffTile& t
   } else if (f.kind == DIFF_VEC) {
     if (i0 >= i1) return;  // no row of the strip (uniform over the workgroup)
     if (f.dtype == WB_F32)
-      vec_tile<4, T, P, false>(s, f.cols, f.base, i0, i1, t.j0, out);
+      vec_tile<4, T, P, false, true>(s, f.cols, f.base, i0, i1, t.j0, out);
     else
-      vec_tile<8, T, P, false>(s, f.cols, f.base, i0, i1, t.j0, out);
+      vec_tile<8, T, P, false, true>(s, f.cols, f.base, i0, i1, t.j0, out);
   } else if (f.kind == DIFF_RAGGED) {
     if (i0 >= i1) return;  // no row of the strip (uniform over the workgroup)
     if (f.dtype == WB_F32)
-      vec_tile<4, T, P, true>(s, f.cols, f.base, i0, i1, t.j0, out);
+      vec_tile<4, T, P, true, true>(s, f.cols, f.base, i0, i1, t.j0, out);
     else
-      vec_tile<8, T, P, true>(s, f.cols, f.base, i0, i1, t.j0, out);
+      vec_tile<8, T, P, true, true>(s, f.cols, f.base, i0, i1, t.j0, out);
   } else {
     elem_tile<T, P>(s, f.dtype, f.rows, f.cols, f.base, t.i0, t.j0, out);
   }
