@@ -247,24 +247,20 @@ struct Unaligned {
   typedef const __attribute__((address_space(1))) type* const_ptr;
 };
 
-template <typename T, int kAlign>
+template <typename T, int kAlign, bool kNt = WB_NT_LOAD != 0>
 __device__ __forceinline__ T ld_at(const char* p) {
   const auto q = (typename Unaligned<T, kAlign>::const_ptr)(reinterpret_cast<uintptr_t>(p));
-#if WB_NT_LOAD
-  return __builtin_nontemporal_load(q);
-#else
+  if (kNt) return __builtin_nontemporal_load(q);
   return *q;
-#endif
 }
 
-template <typename T, int kAlign, typename P>
+template <typename T, int kAlign, bool kNt = WB_NT_STORE != 0, typename P>
 __device__ __forceinline__ void st_at(T v, P* p) {
   const auto q = (typename Unaligned<T, kAlign>::ptr)(reinterpret_cast<uintptr_t>(p));
-#if WB_NT_STORE
-  __builtin_nontemporal_store(v, q);
-#else
-  *q = v;
-#endif
+  if (kNt)
+    __builtin_nontemporal_store(v, q);
+  else
+    *q = v;
 }
 
 // One chunk of a rectangle whose rows sit at any element address (flat shards
@@ -379,23 +375,31 @@ __device__ __forceinline__ u32x4 column8(const u32x4 (&a)[8], int j) {
 // each lane an 8 x 8 sub-tile that it loads as eight 16-byte rows, transposes
 // in registers and stores as eight 16-byte rows, at any element address on
 // both sides. Lanes 8i..8i+7 cover one 128-byte span of a row on both sides.
-__device__ void run_transpose16(const Task& t, const char* src, char* dst, uint32_t w) {
+// Spans that are no whole lines share lines with their neighbours', so the
+// stores carry no non-temporal hint (the parts of a line meet in the L2), and
+// the loads only where the spans are whole (kNt): with it, 4 transposes of 4097
+// x 4099 took 146 (bf16), 292 (fp32), 203 (fp32 -> bf16) and 256 us (bf16 ->
+// fp32) against 128, 200, 157 and 186 through LDS tiles without; now 85, 203,
+// 131 and 157. Whole spans (4096 x 4096, fp32 -> bf16): 79, 137 through LDS, 95
+// with plain loads.
+template <bool kNt>
+__device__ __forceinline__ void run_transpose16(const Task& t, const char* src, char* dst, uint32_t w) {
   const uint32_t l = threadIdx.x & 63;
   if (w * 64 >= t.rows) return;
   const uint32_t c0 = 8 * (l & 7), r0 = w * 64 + 8 * (l >> 3);
   u32x4 a[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
-    a[i] = ld_at<u32x4, 2>(src + (uint64_t(r0 + i) * t.src_ld + c0) * 2);
+    a[i] = ld_at<u32x4, 2, kNt>(src + (uint64_t(r0 + i) * t.src_ld + c0) * 2);
 #pragma unroll
   for (int j = 0; j < 8; ++j)
-    st_at<u32x4, 2>(column8(a, j), dst + (uint64_t(c0 + j) * t.dst_ld + r0) * 2);
+    st_at<u32x4, 2, false>(column8(a, j), dst + (uint64_t(c0 + j) * t.dst_ld + r0) * 2);
 }
 
 // dst[c][r] = cvt(src[r][c]) with fp32 on at least one side, (32..128) rows x
 // 32 columns: the same with 4 x 4 sub-tiles and 32 x 32 tiles, a 16-byte row
 // of a sub-tile on each fp32 side and an 8-byte one on a bf16 side.
-template <int kSs, int kDs>
+template <int kSs, int kDs, bool kNt>
 __device__ __forceinline__ void run_transpose4(const Task& t, const char* src, char* dst, uint32_t w) {
   const uint32_t l = threadIdx.x & 63;
   if (w * 32 >= t.rows) return;
@@ -405,9 +409,9 @@ __device__ __forceinline__ void run_transpose4(const Task& t, const char* src, c
   for (int i = 0; i < 4; ++i) {
     const char* p = src + (uint64_t(r0 + i) * t.src_ld + c0) * kSs;
     if (kSs == 4) {
-      a[i] = ld_at<u32x4, 2>(p);
+      a[i] = ld_at<u32x4, 2, kNt>(p);
     } else {
-      const u32x2 x = ld_at<u32x2, 2>(p);
+      const u32x2 x = ld_at<u32x2, 2, kNt>(p);
       a[i] = u32x4{x.x << 16, x.x & 0xFFFF0000u, x.y << 16, x.y & 0xFFFF0000u};
     }
   }
@@ -415,20 +419,34 @@ __device__ __forceinline__ void run_transpose4(const Task& t, const char* src, c
   for (int j = 0; j < 4; ++j) {
     char* p = dst + (uint64_t(c0 + j) * t.dst_ld + r0) * kDs;
     if (kDs == 4) {
-      st_at<u32x4, 2>(u32x4{a[0][j], a[1][j], a[2][j], a[3][j]}, p);
+      st_at<u32x4, 2, false>(u32x4{a[0][j], a[1][j], a[2][j], a[3][j]}, p);
     } else {
-      st_at<u32x2, 2>(u32x2{pack_bf16x2(__uint_as_float(a[0][j]), __uint_as_float(a[1][j])),
-                            pack_bf16x2(__uint_as_float(a[2][j]), __uint_as_float(a[3][j]))},
-                      p);
+      st_at<u32x2, 2, false>(u32x2{pack_bf16x2(__uint_as_float(a[0][j]), __uint_as_float(a[1][j])),
+                                   pack_bf16x2(__uint_as_float(a[2][j]), __uint_as_float(a[3][j]))},
+                             p);
     }
   }
 }
 
-__device__ void run_transpose4_any(const Task& t, const char* src, char* dst, uint32_t w) {
+template <bool kNt>
+__device__ __forceinline__ void run_transpose4_any(const Task& t, const char* src, char* dst, uint32_t w) {
   if (t.sdt == WB_F32)
-    t.ddt == WB_F32 ? run_transpose4<4, 4>(t, src, dst, w) : run_transpose4<4, 2>(t, src, dst, w);
+    t.ddt == WB_F32 ? run_transpose4<4, 4, kNt>(t, src, dst, w) : run_transpose4<4, 2, kNt>(t, src, dst, w);
   else
-    run_transpose4<2, 4>(t, src, dst, w);
+    run_transpose4<2, 4, kNt>(t, src, dst, w);
+}
+
+// Register transposes: w is the tile of the item. A tile's spans of the source
+// are whole lines (or aligned halves) where the item's first and its pitch are
+// multiples of their size.
+__device__ void run_register_transpose(const Task& t, const char* src, char* dst, uint32_t w) {
+  const int ss = dt_bytes(t.sdt);
+  const uint32_t span = uint32_t(t.cols) * ss;  // 64 or 128 bytes
+  const bool whole = ((uint32_t(reinterpret_cast<uintptr_t>(src)) | t.src_ld * uint32_t(ss)) & (span - 1)) == 0;
+  if (t.kind == TASK_TRANSPOSE16)
+    whole ? run_transpose16<WB_NT_LOAD != 0>(t, src, dst, w) : run_transpose16<false>(t, src, dst, w);
+  else
+    whole ? run_transpose4_any<WB_NT_LOAD != 0>(t, src, dst, w) : run_transpose4_any<false>(t, src, dst, w);
 }
 
 }  // namespace
@@ -489,8 +507,10 @@ __global__ __launch_bounds__(kThreads) void wb_tasks_kernel(const Task* __restri
     case TASK_ROWS: run_rows_any(t, src, dst, chunk); break;
     case TASK_SCALAR: if (chunk == 0) run_scalar(t, src, dst); break;
     case TASK_TRANSPOSE: run_transpose(t, src, dst, chunk); break;
-    case TASK_TRANSPOSE16: run_transpose16(t, src, dst, chunk * (kThreads / 64) + (threadIdx.x >> 6)); break;
-    case TASK_TRANSPOSE4: run_transpose4_any(t, src, dst, chunk * (kThreads / 64) + (threadIdx.x >> 6)); break;
+    case TASK_TRANSPOSE16:
+    case TASK_TRANSPOSE4:
+      run_register_transpose(t, src, dst, chunk * (kThreads / 64) + (threadIdx.x >> 6));
+      break;
     default: break;
   }
 }
