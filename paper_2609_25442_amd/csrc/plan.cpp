@@ -144,6 +144,14 @@ struct TaskSink {
     }
   }
 
+  // Elements of a TASK_ROWS item of units of V elements, es bytes each on the wider
+  // side: 4 units short of the chunks of an aligned item (a cast's are two units
+  // a lane wide), so that heads and remainders need no more of them than it has.
+  int64_t rows_item(int64_t V, int es, bool cast) const {
+    const int64_t aligned = task_bytes / es / V;
+    return std::max<int64_t>(V, ((cast ? aligned / 2 : aligned) - 4) * V);
+  }
+
   // Rows at any element address (TASK_ROWS), in items of at most task_bytes and
   // of the chunks an aligned item has; rows too narrow for a unit go element
   // by element in shorter items (a wave takes a whole one).
@@ -159,10 +167,7 @@ struct TaskSink {
                std::min(nc, cols - c));
       return;
     }
-    // 4 units short of the chunks of an aligned item (a cast's are two units a
-    // lane wide), so that heads and remainders need no more of them than it has
-    const int64_t V = rows_unit(sdt, ddt), aligned = task_bytes / std::max(ss, ds) / V;
-    const int64_t per_task = std::max<int64_t>(V, ((sdt == ddt ? aligned : aligned / 2) - 4) * V);
+    const int64_t V = rows_unit(sdt, ddt), per_task = rows_item(V, std::max(ss, ds), sdt != ddt);
     // column cuts at destination multiples of the unit, no piece narrower than one
     const int64_t head = int64_t((V * ds - doff % (V * ds)) % (V * ds)) / ds;
     const int64_t nr = std::max<int64_t>(1, per_task / ((cols + V - 1) / V * V + V));
@@ -179,28 +184,58 @@ struct TaskSink {
       }
   }
 
+  // Whether a run of n elements that starts at the same phase on both sides (head
+  // elements before the first 16-byte boundary of both) goes as a vector item with
+  // single elements at its ends, instead of as TASK_ROWS. Casts in TASK_ROWS
+  // take twice the workgroups of a vector item, and the hardware starts about
+  // 4.7 of them in a nanosecond: where a launch's power of two leaves many of
+  // them idle (10,004 fp32 elements: 64 for 40), that bounds them, not HBM. Gathered
+  // runs of 10,004 and 65,540 fp32 -> bf16 547 and 501 us, as vectors 419 and
+  // 400; of 1,000,004, where few are idle, 396 and 428. Bf16 -> fp32 vectors are
+  // slower by themselves (65,540: 514 and 564 us, 10,004: 550 and 465). Casts that
+  // start on whole lines: 0.8 GB 135 and 123 us. Fp32 copies: 0.8 GB 166 and 162
+  // us; shorter ones and bf16 copies are even.
+  bool vector_run(uint8_t kind, int es, int64_t head, int64_t n, uint64_t soff, uint64_t doff) const {
+    if (head < 0 || n < 8192) return false;
+    if (kind == TASK_COPY16) return es == 4 && n >= 65536;
+    const int64_t V = 4, items = (n + rows_item(V, 4, true) - 1) / rows_item(V, 4, true);
+    const int64_t one = std::min(n, rows_item(V, 4, true)), needed = (n + V * kChunkThreads - 1) / (V * kChunkThreads);
+    int64_t per = 1;
+    while (per * V * kChunkThreads < one) per <<= 1;
+    if (kind == TASK_BF16_F32) return 20 * items * per > 31 * needed;
+    return 5 * items * per > 6 * needed || (soff % 128 == 0 && doff % 128 == 0);
+  }
+
   // rows x cols elements; src/dst row strides in elements; offsets in bytes.
   // 16-byte aligned rectangles of whole vectors take the vector kinds, all
-  // others TASK_ROWS.
+  // others TASK_ROWS, but for the runs of vector_run.
   void copy_rect(int sidx, uint64_t soff, int64_t sld, int sdt, int didx, uint64_t doff, int64_t dld, int ddt,
                  int64_t rows, int64_t cols) {
     const int ss = dtype_bytes(sdt), ds = dtype_bytes(ddt);
     const int64_t per_task = std::max<int64_t>(16, task_bytes / std::max(ss, ds));
-    uint8_t kind;
-    int64_t v;
+    uint8_t kind = 0;
+    int64_t v = 1;
     const bool vk = vector_kind(sdt, ddt, kind, v);
     if (rows == 1 || (cols == sld && cols == dld)) {
       // contiguous on both sides: one linear run
       const int64_t n = rows * cols;
-      if (!vk || soff % 16 || doff % 16 || n % v) {
+      int64_t head = -1;
+      for (int64_t e = 0; vk && head < 0 && e < v; ++e)
+        if ((soff + e * ss) % 16 == 0 && (doff + e * ds) % 16 == 0) head = e;
+      if ((head != 0 || n % v) && !(vk && vector_run(kind, ss, head, n, soff, doff))) {
         push_rows(sidx, soff, n, sdt, didx, doff, n, ddt, 1, n);
         return;
       }
-      const int64_t chunk = std::max<int64_t>(v, per_task / v * v);
-      for (int64_t a = 0; a < n; a += chunk) {
-        const int64_t len = std::min(chunk, n - a);
+      const auto ends = [&](int64_t a, int64_t len) {
+        if (len) push(TASK_SCALAR, sidx, soff + a * ss, 0, sdt, didx, doff + a * ds, 0, ddt, 1, len);
+      };
+      const int64_t end = head + (n - head) / v * v, chunk = std::max<int64_t>(v, per_task / v * v);
+      ends(0, head);
+      for (int64_t a = head; a < end; a += chunk) {
+        const int64_t len = std::min(chunk, end - a);
         push_vec(kind, sidx, soff + a * ss, len, sdt, didx, doff + a * ds, len, ddt, 1, len);
       }
+      ends(end, n - end);
       return;
     }
     const bool vec = vk && soff % 16 == 0 && doff % 16 == 0 && cols % v == 0 && (sld * ss) % 16 == 0 &&

@@ -505,6 +505,20 @@ def test_plan_threads_change_nothing(budget, G, monkeypatch):
     assert p.work_digest() != next(iter(seen))[0]
 
 
+@pytest.mark.parametrize("tdt,rdt,n,items", [
+    ("f32", "bf16", 10004, 2), ("f32", "bf16", 10000, 1), ("f32", "bf16", 8188, 1), ("f32", "bf16", 65540, 2),
+    ("bf16", "f32", 10004, 2), ("bf16", "f32", 65540, 3), ("f32", "f32", 70001, 3), ("f32", "f32", 10001, 1),
+    ("bf16", "bf16", 100003, 1)])
+def test_runs_of_one_phase(tdt, rdt, n, items):
+    """A run that starts on 16 bytes on both sides and ends between: a vector item
+    and its last elements where that is the faster form, else row items."""
+    T, R = wb.Layout.create([("X", 1, n)], 1), wb.Layout.create([("X", 1, n)], 1)
+    for L, dt in ((T, tdt), (R, rdt)):
+        L.add_local(0, "x", dt, 1, 1, n)
+        L.add_placement(0, 0, 0, 1, 0, n, 0, 0, n)
+    assert wb.Plan(T, R, wb.RECEIVER, 0).work_counts()[0] == items
+
+
 def test_c_client_compiles_and_plans(tmp_path):
     """include/wb.h is a C header: a C99 program using it (tests/c_abi_plan.c)
     compiles without warnings under -pedantic, links against libwb.so and, on

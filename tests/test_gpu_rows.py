@@ -41,7 +41,8 @@ def _layouts(rows, wa, wb_, base, pad, tdt, rdt):
 @pytest.mark.parametrize("rows,wa,wb_,base,pad", [
     (1, 3, 4, 1, 0), (3, 5, 7, 1, 1), (5, 8, 9, 3, 2), (7, 4, 15, 0, 1), (2, 16, 17, 7, 0), (130, 63, 66, 5, 3),
     (33, 511, 514, 1, 0), (9, 1024, 1025, 8, 8), (257, 96, 104, 8, 8), (1, 70001, 131075, 1, 0), (3, 65537, 140003, 2, 5),
-    (40, 1721, 1500, 11, 0)])
+    (40, 1721, 1500, 11, 0), (1, 10004, 65540, 4, 0), (1, 131072, 70001, 8, 0), (1, 8191, 8192, 8, 0),
+    (1, 8196, 100012, 12, 0)])
 def test_rows_at_any_element(rows, wa, wb_, base, pad, tdt, rdt):
     cat, tr, ro = _layouts(rows, wa, wb_, base, pad, tdt, rdt)
     roundtrip(tr, ro, _values(cat, tdt), label=f"rows-{rows}x{wa}+{wb_}-{base}-{pad}-{tdt}-{rdt}")
