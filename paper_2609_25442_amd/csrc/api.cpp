@@ -749,14 +749,12 @@ int wb_unpack_round_noalloc(wb_plan_t* P, int32_t round, const void* recv_buf, v
     if (!P) return set_error(WB_EINVAL, "null plan");
     if (P->role != WB_RECEIVER) return set_error(WB_EINVAL, "unpacking needs a receiver plan");
     if (round < 0 || round >= static_cast<int>(P->rounds.size())) return set_error(WB_EINVAL, "round out of range");
-    // the round's tables in the scratch array: [pointer table | tasks | blocks | pieces]
+    // the round's tables, staged in the scratch array
     const uint32_t t0 = P->round_tasks[round], t1 = P->round_tasks[round + 1];
     const uint32_t b0 = P->round_qblocks[round], b1 = P->round_qblocks[round + 1];
     const uint32_t q0 = P->round_qpieces[2 * round], q1 = P->round_qpieces[2 * round + 1];
-    const size_t off_tasks = align256(sizeof(uint64_t) * (P->n_locals + 1));
-    const size_t off_blocks = align256(off_tasks + sizeof(wb::Task) * (t1 - t0));
-    const size_t off_pieces = align256(off_blocks + sizeof(wb::QBlock) * (b1 - b0));
-    const size_t need = off_pieces + sizeof(wb::QPiece) * (q1 - q0);
+    const wb::RoundTables tables = wb::round_tables(*P, round);
+    const size_t off_tasks = tables.tasks, off_blocks = tables.blocks, off_pieces = tables.pieces, need = tables.bytes;
     void* base = nullptr;
     size_t cap = 0;
     hipError_t e = static_cast<hipError_t>(wb::scratch_address(&base, &cap));

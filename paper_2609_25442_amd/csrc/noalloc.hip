@@ -18,7 +18,6 @@
 namespace wb {
 namespace {
 
-constexpr size_t kScratchBytes = size_t(32) << 20;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];

@@ -106,6 +106,7 @@ void validate_layout(const wb_layout_t& L, bool exact_cover, const char* side) {
 struct TaskSink {
   std::vector<Task>& out;
   int64_t task_bytes;
+  bool fewest = false;  // as few items as task_bytes allows, whatever workgroups they need (trim_round)
 
   void push(uint8_t kind, int sidx, uint64_t soff, uint32_t sld, int sdt, int didx, uint64_t doff, uint32_t dld,
             int ddt, int64_t rows, int64_t cols) {
@@ -148,6 +149,7 @@ struct TaskSink {
   // side: 4 units short of the chunks of an aligned item (a cast's are two units
   // a lane wide), so that heads and remainders need no more of them than it has.
   int64_t rows_item(int64_t V, int es, bool cast) const {
+    if (fewest) return std::max<int64_t>(16, task_bytes / es);
     const int64_t aligned = task_bytes / es / V;
     return std::max<int64_t>(V, ((cast ? aligned / 2 : aligned) - 4) * V);
   }
@@ -159,7 +161,7 @@ struct TaskSink {
                  int64_t rows, int64_t cols) {
     const int ss = dtype_bytes(sdt), ds = dtype_bytes(ddt);
     if (ss < 2 || ds < 2 || cols < rows_unit(sdt, ddt)) {
-      const int64_t per = 4096, nc = std::min(cols, per), nr = std::max<int64_t>(1, per / nc);
+      const int64_t per = fewest ? rows_item(1, std::max(ss, ds), false) : 4096, nc = std::min(cols, per), nr = std::max<int64_t>(1, per / nc);
       for (int64_t r = 0; r < rows; r += nr)
         for (int64_t c = 0; c < cols; c += nc)
           push(TASK_SCALAR, sidx, soff + (r * sld + c) * ss, static_cast<uint32_t>(sld), sdt, didx,
@@ -170,7 +172,7 @@ struct TaskSink {
     const int64_t V = rows_unit(sdt, ddt), per_task = rows_item(V, std::max(ss, ds), sdt != ddt);
     // column cuts at destination multiples of the unit, no piece narrower than one
     const int64_t head = int64_t((V * ds - doff % (V * ds)) % (V * ds)) / ds;
-    const int64_t nr = std::max<int64_t>(1, per_task / ((cols + V - 1) / V * V + V));
+    const int64_t nr = std::max<int64_t>(1, per_task / (fewest ? cols : (cols + V - 1) / V * V + V));
     for (int64_t r = 0; r < rows; r += nr)
       for (int64_t c = 0; c < cols;) {
         int64_t end = cols - c <= per_task + head ? cols : c == 0 ? per_task + head : c + per_task;
@@ -293,7 +295,7 @@ struct TaskSink {
                        int64_t R, int64_t C) {
     const int ss = dtype_bytes(sdt), ds = dtype_bytes(ddt);
     const int64_t E = ss == 2 && ds == 2 ? 64 : 32;
-    if (ss >= 2 && ds >= 2 && R >= E && C >= E) {
+    if (ss >= 2 && ds >= 2 && R >= E && C >= E && !(fewest && E == 32)) {
       const uint8_t kind = E == 64 ? TASK_TRANSPOSE16 : TASK_TRANSPOSE4;
       for (int64_t c0 = 0; c0 < C; c0 += E) {
         const int64_t c = std::min(c0, C - E);
@@ -602,6 +604,19 @@ void build_qblocks(const wb_layout_t& trainer, const Rank& R, wb_plan_t& P, cons
   });
 }
 
+// The work items of what a segment brings to a local that is not quantised.
+void receive_items(TaskSink& sink, const Segment& g, const Placement& q, int sdt, int ddt) {
+  const int ds = dtype_bytes(ddt);
+  const int64_t C = g.x.cols(), Rr = g.x.rows();
+  if (!q.tr) {
+    const int64_t start = q.base + (g.x.r0 - q.r0) * q.ld + (g.x.c0 - q.c0);
+    sink.copy_rect(0, g.recv_off, C, sdt, 1 + q.u, uint64_t(start) * ds, q.ld, ddt, Rr, C);
+  } else {
+    const int64_t start = q.base + (g.x.c0 - q.c0) * q.ld + (g.x.r0 - q.r0);
+    sink.transpose_rect(0, g.recv_off, C, sdt, 1 + q.u, uint64_t(start) * ds, q.ld, ddt, Rr, C);
+  }
+}
+
 void build_rank_view(const wb_layout_t& trainer, const wb_layout_t& rollout, wb_plan_t& P) {
   TaskSink sink{P.tasks, env_task_bytes()};
   const int nrounds = static_cast<int>(P.rounds.size());
@@ -674,15 +689,8 @@ void build_rank_view(const wb_layout_t& trainer, const wb_layout_t& rollout, wb_
       qspans.push_back({&g, e, row0, col0});
       continue;
     }
-    const int ddt = dl.dtype, ds = dtype_bytes(ddt);
-    P.write_bytes += g.x.numel() * ds;
-    if (!q.tr) {
-      const int64_t start = q.base + (g.x.r0 - q.r0) * q.ld + (g.x.c0 - q.c0);
-      sink.copy_rect(0, g.recv_off, C, sdt, 1 + q.u, uint64_t(start) * ds, q.ld, ddt, Rr, C);
-    } else {
-      const int64_t start = q.base + (g.x.c0 - q.c0) * q.ld + (g.x.r0 - q.r0);
-      sink.transpose_rect(0, g.recv_off, C, sdt, 1 + q.u, uint64_t(start) * ds, q.ld, ddt, Rr, C);
-    }
+    P.write_bytes += g.x.numel() * dtype_bytes(dl.dtype);
+    receive_items(sink, g, q, sdt, dl.dtype);
   }
   P.round_tasks[k + 1] = static_cast<uint32_t>(P.tasks.size());
   }
@@ -703,6 +711,33 @@ void build_rank_view(const wb_layout_t& trainer, const wb_layout_t& rollout, wb_
     }
   }
   if (nblocks > 0) build_qblocks(trainer, R, P, qspans, nblocks);
+}
+
+// A round whose tables pass the library's scratch array only because row items
+// are cut for even launches (a cast's hold half as much, narrow rows' 4096
+// elements) gets the fewest items instead, so that the allocation-free call
+// takes it: its launch may leave more workgroups idle.
+void trim_round(const wb_layout_t& trainer, const wb_layout_t& rollout, wb_plan_t& P, int k) {
+  const RoundTables T = round_tables(P, k);
+  const size_t had = P.round_tasks[k + 1] - P.round_tasks[k];
+  const auto with = [&](size_t items) { return (T.tasks + sizeof(Task) * items + 255) / 256 * 256 + T.bytes - T.blocks; };
+  if (T.bytes <= kScratchBytes || with(0) > kScratchBytes) return;
+  const Rank& R = rollout.ranks[P.rank];
+  std::vector<Task> few;
+  TaskSink sink{few, env_task_bytes(), true};
+  for (const Segment& g : P.segs) {
+    if (g.round != k || g.d != P.rank) continue;
+    const Placement& q = R.pls[g.dst_pl];
+    if (R.locals[q.u].block <= 0)
+      receive_items(sink, g, q, wire_dtype(trainer, P.segs, g), R.locals[q.u].dtype);
+  }
+  if (few.size() >= had || with(few.size()) > kScratchBytes) return;
+  const uint32_t less = static_cast<uint32_t>(had - few.size());
+  std::copy(few.begin(), few.end(), P.tasks.begin() + P.round_tasks[k]);
+  P.tasks.erase(P.tasks.begin() + P.round_tasks[k] + few.size(), P.tasks.begin() + P.round_tasks[k + 1]);
+  for (size_t j = k + 1; j < P.round_tasks.size(); ++j) P.round_tasks[j] -= less;
+  for (auto& r : P.round_fwd)
+    for (uint32_t& t : r) t -= less;
 }
 
 // Every byte a work item touches lies inside its buffer, and vector work items
@@ -1313,6 +1348,8 @@ void build_plan(const wb_layout_t& trainer, const wb_layout_t& rollout, int role
   P.role = role;
   P.rank = rank;
   build_rank_view(trainer, rollout, P);
+  if (role == WB_RECEIVER)
+    for (int k = 0; k < nrounds; ++k) trim_round(trainer, rollout, P, k);
   // each launch range ordered by work item class (planner order within a class)
   auto partition = [&](uint32_t a, uint32_t b) {
     const auto first = P.tasks.begin() + a, last = P.tasks.begin() + b;

@@ -433,7 +433,23 @@ int launch_qblocks(const QBlock* blocks, uint32_t n, uint32_t nfull, uint32_t np
 const char* hip_error_string(int err);
 // noalloc.hip: the library's per-GPU scratch array for allocation-free calls
 // (its address on the current device, found once per device, and its size)
+constexpr size_t kScratchBytes = size_t(32) << 20;
 int scratch_address(void** out, size_t* bytes);
+
+// A round's tables there: [pointer table | work items | fp8 blocks | pieces],
+// each from a multiple of 256 bytes.
+struct RoundTables {
+  size_t tasks, blocks, pieces, bytes;
+};
+inline RoundTables round_tables(const wb_plan_t& P, int k) {
+  const auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
+  RoundTables t;
+  t.tasks = up(sizeof(uint64_t) * (P.n_locals + 1));
+  t.blocks = up(t.tasks + sizeof(Task) * (P.round_tasks[k + 1] - P.round_tasks[k]));
+  t.pieces = up(t.blocks + sizeof(QBlock) * (P.round_qblocks[k + 1] - P.round_qblocks[k]));
+  t.bytes = t.pieces + sizeof(QPiece) * (P.round_qpieces[2 * k + 1] - P.round_qpieces[2 * k]);
+  return t;
+}
 // dev[0] = 0, dev[1 + i] = ptrs[i] for i < n, written by kernels whose
 // arguments carry the pointers (no host buffer outlives the call)
 int launch_store_table(uint64_t* dev, const void* const* ptrs, int n, void* stream);

@@ -519,6 +519,34 @@ def test_runs_of_one_phase(tdt, rdt, n, items):
     assert wb.Plan(T, R, wb.RECEIVER, 0).work_counts()[0] == items
 
 
+def _beside(r, c, pad):
+    """X [r, c] fp32, into the columns from ``pad`` of a bf16 tensor pad + c wide
+    whose first columns are Y's."""
+    cat = [("X", r, c), ("Y", r, pad)]
+    T, R = wb.Layout.create(cat, 1), wb.Layout.create(cat, 1)
+    for t, (n, k, w) in enumerate(cat):
+        T.add_local(0, n, "f32", 1, k, w)
+        T.add_placement(0, t, 0, k, 0, w, t, 0, w)
+    R.add_local(0, "x", "bf16", 1, r, pad + c)
+    R.add_placement(0, 0, 0, r, 0, c, 0, pad, pad + c)
+    R.add_placement(0, 1, 0, r, 0, pad, 0, 0, pad + c)
+    return T, R
+
+
+@pytest.mark.parametrize("task_bytes,r,c,most", [
+    (1024, 1, 150_000_000, 150_000_000 // 256 + 3),          # a cast at an odd phase
+    (1 << 18, 1_000_000_000, 3, 1_000_000_000 // 21845 + 1_000_000_000 // 65536 + 2)])  # rows below a unit
+def test_row_items_fit_the_scratch_array(task_bytes, r, c, most, monkeypatch):
+    """Row items are cut shorter than task_bytes allows, for the launch's sake; a
+    round whose tables would pass the 32 MiB of the allocation-free call only for
+    that has the longest ones. A smaller round keeps the short ones."""
+    monkeypatch.setenv("WB_TASK_BYTES", str(task_bytes))
+    p = wb.Plan(*_beside(r, c, 1), wb.RECEIVER, 0)
+    assert p.work_counts()[0] <= most and p.workspace_bytes < 32 << 20
+    small = wb.Plan(*_beside(max(1, r // 8), c if r > 1 else c // 8, 1), wb.RECEIVER, 0)
+    assert p.work_counts()[0] // 8 < small.work_counts()[0] and small.workspace_bytes < 32 << 20
+
+
 def test_c_client_compiles_and_plans(tmp_path):
     """include/wb.h is a C header: a C99 program using it (tests/c_abi_plan.c)
     compiles without warnings under -pedantic, links against libwb.so and, on

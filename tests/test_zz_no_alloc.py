@@ -100,6 +100,27 @@ def test_noalloc_transposed_rollout_tiles(rows, cols):
     _compare_layouts(f"transposed {rows}x{cols}", tr, ro, 0, "bf16", 0, 4)
 
 
+@pytest.mark.parametrize("n", [100_000_000, 30_000_000])
+def test_noalloc_tables_at_the_array_size(n, monkeypatch):
+    # a cast at an odd phase, cut into enough items that the tables of 100 M
+    # elements fit the array only with the longest ones
+    monkeypatch.setenv("WB_TASK_BYTES", "1024")
+    cat = [CkptTensor("X", 1, n), CkptTensor("Y", 1, 1)]
+    tr = Layout(cat, [RankLayout([Local("a", "f32", 1, 1, n), Local("b", "f32", 1, 1, 1)],
+                                 [Placement(0, 0, 1, 0, n, 0, 0, n), Placement(1, 0, 1, 0, 1, 1, 0, 1)])])
+    ro = Layout(cat, [RankLayout([Local("x", "bf16", 1, 1, n + 1)],
+                                 [Placement(0, 0, 1, 0, n, 0, 1, n), Placement(1, 0, 1, 0, 1, 0, 0, 1)])])
+    tr, ro = to_wb(tr), to_wb(ro)
+    p = wb.Plan(tr, ro, wb.RECEIVER, 0)
+    say(f"[noalloc] {n} elements: {p.work_counts()[0]} items")
+    recv = _receive_buffers(p, "f32", 5)[0]
+    got = wb.allocate_locals(ro, 0)
+    p.unpack_round_noalloc(0, recv, got)
+    torch.cuda.synchronize()
+    want = recv[:4 * n].view(torch.float32).to(torch.bfloat16)
+    assert torch.equal(_raw(got[0].reshape(-1)[1:]), _raw(want))
+
+
 def test_noalloc_refuses_tables_beyond_the_array():
     # the DeepSeek-V3 receiver in one round needs ~72 MB of tables: refused
     # before its (null) pointers are looked at; in 4 GiB rounds it fits
