@@ -1047,24 +1047,66 @@ __device__ __forceinline__ void qblock_wide(const QBlock& b, const BlockSource<k
   }
 }
 
-// A block whose pieces are neither all bf16 nor all fp32: element by element
-// from the piece list, 8 rows of 8 columns per thread.
-__device__ void qblock_mixed(const QBlock& b, const QPiece* __restrict__ pieces, const uint64_t* __restrict__ ptrs,
-                             const char* recv) {
+// A block whose pieces are neither all bf16 nor all fp32: 8 rows of 8 columns
+// per thread, held as fp32. A row's chunk of 8 that lies in one piece is one
+// (bf16) or two (fp32) loads of 16 bytes, all in flight together; the others are
+// searched for element by element. 8192 x 8192 in bands of 64 rows of both types
+// took 343 us when every element was searched for and 66 now, in strips of 64
+// columns 521 and 84.
+template <bool kStaged>
+__device__ __forceinline__ void qblock_mixed(const QBlock& b, const QPiece* pcs, const uint8_t* row_piece,
+                                             const uint64_t* __restrict__ ptrs, const char* recv) {
   constexpr int R = 8, kStep = 16;
   static_assert(kQBlockThreads == 16 * kStep, "block mapping");
   __shared__ float wave_max[kQBlockThreads / 64];
   const int rows = b.rows_m1 + 1, cols = b.cols_m1 + 1;
   const int cg = (threadIdx.x & 15) * 8, rb = threadIdx.x >> 4;
+  const uint32_t n = b.npieces;
+  u32x4 lo[R], hi[R];
+  unsigned wide = 0, odd = 0;  // bit k: row k's chunk is fp32; needs single elements
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int r = rb + kStep * k;
+    lo[k] = hi[k] = u32x4{0u, 0u, 0u, 0u};
+    if (r >= rows || cg >= cols) continue;
+    uint32_t i = kStaged ? row_piece[r] : 0xFF;
+    if (i == 0xFF || cg + 7 >= cols)
+      for (i = 0; i < n; ++i) {
+        const QPiece& p = pcs[i];
+        if (r >= p.r0 && r <= p.r1m1 && cg >= p.c0 && cg + 7 <= p.c1m1) break;
+      }
+    if (i >= n) {
+      odd |= 1u << k;
+      continue;
+    }
+    const QPiece& p = pcs[i];
+    const int es = p.sdt == WB_F32 ? 4 : 2;
+    const char* a = recv + p.src_off + (uint64_t(r - p.r0) * p.src_ld + (cg - p.c0)) * es;
+    lo[k] = ld_at<u32x4, 2>(a);
+    if (es == 4) {
+      wide |= 1u << k;
+      hi[k] = ld_at<u32x4, 2>(a + 16);
+    }
+  }
   float v[R][8], amax = 0.0f;
 #pragma unroll
-  for (int k = 0; k < R; ++k)
+  for (int k = 0; k < R; ++k) {
+    const int r = rb + kStep * k;
+    unpack8(lo[k], v[k]);
+    if ((wide >> k) & 1u) {
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const int r = rb + kStep * k;
-      v[k][m] = r < rows && cg + m < cols ? gather_one(pieces + b.piece0, b.npieces, recv, r, cg + m) : 0.0f;
-      amax = fmaxf(amax, fabsf(v[k][m]));
+      for (int m = 0; m < 4; ++m) {
+        v[k][m] = __uint_as_float(lo[k][m]);
+        v[k][4 + m] = __uint_as_float(hi[k][m]);
+      }
     }
+    if ((odd >> k) & 1u) {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) v[k][m] = cg + m < cols ? gather_one(pcs, n, recv, r, cg + m) : 0.0f;
+    }
+#pragma unroll
+    for (int m = 0; m < 8; ++m) amax = fmaxf(amax, fabsf(v[k][m]));
+  }
   for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = amax;
   __syncthreads();
@@ -1088,10 +1130,7 @@ __device__ __forceinline__ void qblock_one(const QBlock& b, const QPiece* __rest
                            const char* recv) {
   __shared__ QPiece lds_pcs[kLdsPieces];
   __shared__ uint8_t row_piece[128];
-  if (!(b.flags & (QB_BF16_SOURCE | QB_F32_SOURCE))) {
-    qblock_mixed(b, pieces, ptrs, recv);
-    return;
-  }
+  const bool mixed = !(b.flags & (QB_BF16_SOURCE | QB_F32_SOURCE));
   const bool f32 = (b.flags & QB_F32_SOURCE) != 0;
   const uint32_t n = b.npieces;
   if (b.flags & QB_DIRECT) {
@@ -1111,13 +1150,17 @@ __device__ __forceinline__ void qblock_one(const QBlock& b, const QPiece* __rest
       for (uint32_t r = p.r0 + part; r <= p.r1m1; r += parts) row_piece[r] = static_cast<uint8_t>(i);
     __syncthreads();
     const BlockSource<kSourceStaged> S{nullptr, lds_pcs, row_piece, 0u, n};
-    if (f32)
+    if (mixed)
+      qblock_mixed<true>(b, lds_pcs, row_piece, ptrs, recv);
+    else if (f32)
       qblock_wide<true>(b, S, ptrs, recv);
     else
       qblock_wide<false>(b, S, ptrs, recv);
   } else {
     const BlockSource<kSourceList> S{nullptr, pieces + b.piece0, nullptr, 0u, n};
-    if (f32)
+    if (mixed)
+      qblock_mixed<false>(b, pieces + b.piece0, nullptr, ptrs, recv);
+    else if (f32)
       qblock_wide<true>(b, S, ptrs, recv);
     else
       qblock_wide<false>(b, S, ptrs, recv);

@@ -94,6 +94,41 @@ def test_mixed_wire_types_in_one_block():
     assert np.array_equal(s.cpu().numpy(), scales)
 
 
+def _grid(rows, cols, h, w):
+    return [(r, min(rows, r + h), c, min(cols, c + w)) for r in range(0, rows, h) for c in range(0, cols, w)]
+
+
+@pytest.mark.parametrize("rows,cols,h,w", [(200, 264, 30, 264), (200, 261, 7, 261), (140, 130, 140, 13), (130, 131, 61, 45),
+                                           (128, 128, 4, 16), (128, 128, 1, 64), (129, 127, 5, 8), (40, 6, 3, 6)])
+def test_mixed_wire_types_however_cut(rows, cols, h, w):
+    """Pieces of h rows by w columns, by turns fp32 and bf16 (a rank each): bands,
+    chunks that straddle pieces, ragged edges and more pieces than are staged."""
+    parts = _grid(rows, cols, h, w)
+    dts = ["f32" if (i + i // -(-cols // w)) % 2 else "bf16" for i in range(len(parts))]
+    L = wb.Layout.create([("T", rows, cols)], len(parts))
+    for i, ((r0, r1, c0, c1), dt) in enumerate(zip(parts, dts)):
+        L.add_local(i, "t", dt, 1, r1 - r0, c1 - c0)
+        L.add_placement(i, 0, r0, r1, c0, c1, 0, 0, c1 - c0)
+    R = wb.Layout.create([("T", rows, cols)], 1)
+    R.add_local(0, "q", "f8e4m3", 1, rows, cols, 128)
+    R.add_placement(0, 0, 0, rows, 0, cols, 0, 0, cols)
+    p = wb.Plan(L, R, wb.RECEIVER, 0)
+    p.upload(workspace_for(p))
+    x = torch.randn(rows, cols, generator=torch.Generator().manual_seed(rows)) * 0.02
+    recv = torch.full((p.buffer_bytes,), 0x7F, dtype=torch.uint8)
+    for i, ((r0, r1, c0, c1), dt) in enumerate(zip(parts, dts)):
+        piece = x[r0:r1, c0:c1].to(torch.bfloat16 if dt == "bf16" else torch.float32).contiguous()
+        x[r0:r1, c0:c1] = piece.float()
+        _, off, nb = p.region(i, 0)
+        recv[off:off + nb] = piece.view(-1).view(torch.uint8)
+    q = torch.zeros(rows, cols, dtype=torch.float8_e4m3fn, device="cuda")
+    s = torch.zeros(-(-rows // 128), -(-cols // 128), dtype=torch.float32, device="cuda")
+    p.unpack(recv.cuda(), [q, s])
+    codes, scales = casts.quantize_matrix(x.numpy(), 128)
+    assert np.array_equal(s.cpu().numpy(), scales)
+    assert np.array_equal(q.view(torch.uint8).cpu().numpy(), codes)
+
+
 def test_f32_quotients_next_to_rounding_boundaries():
     """fp32 sources whose quotients lie within a few ulps of every E4M3 rounding
     boundary (midpoints of neighbouring values), over block maxima of every
