@@ -158,7 +158,11 @@ def _load():
 
 
 lib = _load()
-from . import _args  # noqa: E402  (built with libwb.so; needs torch's libraries, loaded above)
+try:  # built with libwb.so; needs torch's libraries, loaded above
+    from . import _args
+except ImportError as e:
+    raise ImportError("_args.so (the argument checks) is not built, or not for this torch "
+                      f"({e}); run `python paper_2609_25442_amd/build.py`") from e
 
 
 def _check(rc: int):

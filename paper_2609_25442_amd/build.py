@@ -7,7 +7,6 @@ needs the library). Always recompiles.
 
 from __future__ import annotations
 
-import importlib.util
 import os
 import subprocess
 import sys
@@ -40,10 +39,13 @@ def _run(cmd):
 
 
 def build_args() -> str:
-    """Compile and link the binding's extension module."""
-    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
-    inc, lib = os.path.join(torch, "include"), os.path.join(torch, "lib")
-    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-isystem", inc, "-isystem",
+    """Compile and link the binding's extension module, by the C++ ABI of the torch it serves."""
+    import torch
+
+    home = os.path.dirname(torch.__file__)
+    inc, lib = os.path.join(home, "include"), os.path.join(home, "lib")
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-isystem", inc, "-isystem",
           os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
           os.path.join(CSRC, "args.cpp"), "-o", ARGS + ".tmp", "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"])
     os.replace(ARGS + ".tmp", ARGS)

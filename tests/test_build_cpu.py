@@ -1,10 +1,12 @@
-"""What the build refuses: kernels read and write rows at element alignment, and
-a load or store that promises the compiler more than that is undefined, also
-where today's instructions would take any address."""
+"""What the build and the import refuse. Kernels read and write rows at element
+alignment, and a load or store that promises the compiler more than that is
+undefined, also where today's instructions would take any address. The
+binding's two binaries come from one build."""
 
 import importlib.util
 import os
 import subprocess
+import sys
 
 import pytest
 
@@ -43,3 +45,18 @@ __global__ void k(const char* p, u4* out) { *out = ld(reinterpret_cast<const u4_
 """)
     r = _compile(str(src))
     assert r.returncode != 0 and "align-mismatch" in r.stderr, r.stderr
+
+
+@pytest.mark.parametrize("args", ["missing", "broken"])
+def test_import_without_the_argument_checks_names_the_build(args, tmp_path):
+    """A tree built before the argument checks came, or a file that does not
+    load, says what to run (as a missing library does)."""
+    pkg = tmp_path / "paper_2609_25442_amd"
+    pkg.mkdir()
+    for name in ("__init__.py", "libwb.so"):
+        os.symlink(os.path.join(ROOT, "paper_2609_25442_amd", name), pkg / name)
+    if args == "broken":
+        (pkg / "_args.so").write_bytes(b"no library")
+    r = subprocess.run([sys.executable, "-c", "import paper_2609_25442_amd"], cwd=tmp_path, capture_output=True, text=True,
+                       env=dict(os.environ, PYTHONPATH=str(tmp_path)))
+    assert r.returncode != 0 and "ImportError" in r.stderr and "paper_2609_25442_amd/build.py" in r.stderr, r.stderr
