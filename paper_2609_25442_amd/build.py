@@ -23,8 +23,9 @@ HIPCC = os.path.join(ROCM, "bin", "hipcc")
 HOST_SOURCES = ["api.cpp", "layout.cpp", "plan.cpp", "probe.cpp"]
 DEVICE_SOURCES = ["kernels.hip", "probe.hip", "noalloc.hip"]
 # no packed fp32 instructions: hipcc would otherwise form v_pk_*_f32 by itself;
-# a pointer that promises more alignment than its data has is an error
-DEVICE_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Werror=align-mismatch",
+# a pointer that promises more alignment than its data has is an error, and so is
+# what nothing uses
+DEVICE_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Werror=align-mismatch", "-Werror=unused",
                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__",
               "-I" + os.path.join(ROCM, "include")]

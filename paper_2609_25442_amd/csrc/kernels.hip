@@ -7,7 +7,8 @@
 //  * wb_tasks_kernel  -- copy/cast work items: 16-byte vectorised row copies,
 //    fp32 -> bf16 (v_cvt_pk_bf16_f32, round to nearest even), bf16 -> fp32,
 //    rows at any element address and width, an element-wise fallback for rows
-//    narrower than a vector, and 64 x 64 tiles transposed through LDS where a trainer stores a shard transposed. Work
+//    narrower than a vector, and tiles transposed in registers (below their
+//    size through LDS) where a trainer stores a shard transposed. Work
 //    items are spread over several one-wave workgroups: a vector kind takes
 //    one per chunk of kChunkVecs vectors, each issuing all of its loads, then
 //    all of its stores, and exiting (no loop, so no wait on the completion of
@@ -22,7 +23,8 @@
 //    q = RN(x / s) computed with one reciprocal per block and a remainder
 //    correction for bf16 sources (exact in the range that reaches E4M3;
 //    checked for every bf16 input pair), two for fp32 ones, IEEE division
-//    outside those forms' range, then v_cvt_pk_fp8_f32. The scale is written by thread 0.
+//    outside those forms' range, then v_cvt_pk_fp8_f32. The scale is written
+//    by thread 0.
 // The work is bandwidth bound: no matrix cores are involved.
 #include <hip/hip_runtime.h>
 
@@ -87,10 +89,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   const bf16x2 h = __builtin_convertvector(f32x2{a, b}, bf16x2);
   return __builtin_bit_cast(uint32_t, h);
-}
-
-__device__ __forceinline__ u32x4 cvt8_f32_bf16(const f32x4& a, const f32x4& b) {
-  return u32x4{pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(b.x, b.y), pack_bf16x2(b.z, b.w)};
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }

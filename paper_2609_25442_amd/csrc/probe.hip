@@ -10,12 +10,16 @@
 // taken as 0 above and left of the tensor) and append its non-zero entries to
 // a list. A slice copy leaves at most 16 of them, so the list is short. The
 // work is cut into tiles, each one workgroup's share of one field:
-//   ELEM  64 rows x 256 columns, one element per lane (any width, any
-//         element-aligned address);
-//   VEC   32 rows (128 batched) x 256 vectors of 16 bytes (8 bf16 or 4 fp32
-//         values), the next row's loads in flight while a row is computed
-//         (cols a multiple of the vector, 16-byte aligned field);
-//   FLAT  one-row fields, 8 x 256 vectors per tile (32 x 256 batched).
+//   VEC   32 rows (batched 128, mostly taken in strips of 32) x 256 vectors of
+//         16 bytes (8 bf16 or 4 fp32 values), the next row's loads in flight
+//         while a row is computed (cols a multiple of the vector, 16-byte
+//         aligned field);
+//   RAGGED  the same for several rows of any width of at least a vector and any
+//         element address: the last vector of a row is moved left inside it;
+//   FLAT  one-row fields of whole aligned vectors, 8 x 256 vectors per tile
+//         (32 x 256 batched);
+//   ELEM  64 rows x 256 columns, one element per lane (the others: rows
+//         narrower than a vector, one row of another width or address).
 // Single-field launches walk one field's tiles with a strided grid; the
 // batched launch takes one tile per workgroup from a table that covers many
 // fields, so all of a rank's tensors take one launch.
@@ -49,7 +53,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kStrip = 64;      // rows of an ELEM tile
-constexpr int kVecStrip = 32;   // rows of a VEC tile
+constexpr int kVecStrip = 32;   // rows of a single-field VEC or RAGGED tile
 constexpr int kFlatUnroll = 8;  // vectors in flight per lane (FLAT)
 
 // Stores of 16 bytes at element alignment (gfx950 stores global memory at any
@@ -83,7 +87,6 @@ __device__ __forceinline__ int64_t vec_at(int64_t v, int64_t cols, int V, int& s
 // The bits of columns that are a vector's own.
 __device__ __forceinline__ unsigned own_columns(int skip) { return ~0u << skip; }
 
-
 // A thread writes 16 bytes: 8 bf16 or 4 fp32 chunks, one workgroup per 4 KiB up
 // to 2^22 workgroups. Bound: HBM write; the stores are plain because the
 // loader reads the identifiers next. 1.05 GB of bf16: 6.9 TB/s one shot, 6.3
@@ -92,7 +95,7 @@ __device__ __forceinline__ unsigned own_columns(int skip) { return ~0u << skip; 
 template <bool kF32>
 __global__ __launch_bounds__(kThreads) void wb_make_ids_kernel(char* dst, int64_t numel, int64_t first_id, int shift,
                                                                uint32_t mask) {
-  constexpr int V = kF32 ? 4 : 8, es = 16 / V;
+  constexpr int V = kF32 ? 4 : 8;
   const int64_t stride = int64_t(gridDim.x) * kThreads, nvec = numel / V;
   const int64_t at = int64_t(blockIdx.x) * kThreads + threadIdx.x;
   for (int64_t i = at; i < nvec; i += stride) {
@@ -706,7 +709,8 @@ __global__ __launch_bounds__(kThreads) void wb_diff2_vec_kernel(const char* __re
   const int64_t nvec = vec_count(cols, V);
   for (int64_t vb = int64_t(blockIdx.x) * kThreads; vb < nvec; vb += int64_t(gridDim.x) * kThreads)
     for (int64_t i0 = int64_t(blockIdx.y) * kVecStrip; i0 < rows; i0 += int64_t(gridDim.y) * kVecStrip)
-      vec_tile<V, int, 1, kRagged, kRagged || V == 8>(s, cols, 0, i0, i0 + kVecStrip < rows ? i0 + kVecStrip : rows, vb, out);
+      vec_tile<V, int, 1, kRagged, kRagged || V == 8>(s, cols, 0, i0, i0 + kVecStrip < rows ? i0 + kVecStrip : rows, vb,
+                                                      out);
   out.flush();
 }
 
@@ -945,7 +949,6 @@ __global__ __launch_bounds__(kThreads) void wb_carry_report_kernel(const int32_t
   }
 }
 
-
 __global__ void wb_zero_count_kernel(unsigned long long* count) { *count = 0; }
 
 // The field and tile tables of a batched launch, written on the device from
@@ -986,8 +989,9 @@ __global__ __launch_bounds__(kThreads) void wb_diff_tables_kernel(DiffField* fie
 
 // VEC and FLAT tiles need whole 16-byte vectors in every pass, RAGGED ones more
 // than one row of at least one vector: 8 fields of 4096 x 4098 bf16 took 390 us
-// a carry pass in ELEM tiles and 100 in RAGGED ones, 1695 and 170 as three held
-// passes. One-row fields stay ELEM (many columns, no rows to keep).
+// a carry pass in ELEM tiles and 94 in RAGGED ones, 1695 and 172 as three held
+// passes. One-row fields of another width or address are ELEM as they were: 16.8
+// M bf16 elements take 52 us (0.65 TB/s), and no other tile was measured on them.
 int tile_kind(const void* const* src, int passes, int dtype, int64_t rows, int64_t cols) {
   const int V = dtype == WB_F32 ? 4 : 8;
   const int other = rows > 1 && cols >= V ? DIFF_RAGGED : DIFF_ELEM;
