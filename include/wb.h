@@ -30,6 +30,11 @@
  *     launch work refuse (WB_EINVAL, before anything is enqueued) null and
  *     misaligned pointers, pageable host memory and unknown addresses, and
  *     device allocations smaller than the call needs.
+ *   - What a call enqueues runs in its stream's order. Its results may be used
+ *     by later work on that stream and on streams ordered after it by events.
+ *     The host, another process and another device (a peer GPU, a NIC) may
+ *     read or write the buffers once the stream, the device or an event
+ *     recorded after the call has been synchronised.
  *   - The library never allocates device memory. It allocates host memory and,
  *     for the pointer tables of wb_pack/wb_unpack, a small pinned host buffer;
  *     wb_unpack_round_noalloc uses a fixed device array the library's code

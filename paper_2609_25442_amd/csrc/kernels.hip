@@ -51,8 +51,8 @@ namespace {
 // (64 KiB) where most blocks go in pairs, three (48 KiB) where most go one per
 // workgroup. Three against two for pairs: 1.5 % slower on 2048 and 4096
 // column rows (0.45 and 0.53 ms launches), 0.5 % faster on 7168; for single
-// fp32 blocks 5.5 % faster (whole unpack 2.06 -> 1.95 ms); four are not to be
-// had with this kernel's registers.
+// fp32 blocks 5.5 % faster (whole unpack 2.06 -> 1.95 ms), four no more (1.94
+// and 1.94 ms).
 constexpr unsigned kQBlockLdsPairs = 65536, kQBlockLdsSingles = 49152;
 
 constexpr int kThreads = kChunkThreads;
@@ -268,8 +268,9 @@ __device__ __forceinline__ void st_at(T v, P* p) {
 // their neighbours, so no row has single elements. Bound: HBM. A bf16 flat
 // shard of a sixth of a 16-layer model (3.2 GB moved), every run at an odd
 // phase: 1974 us element by element, 487 us so (6.6 TB/s, the aligned copy's
-// rate is 6.7); fp32 -> bf16 at widths 1500 and 1721 (0.9 GB): 771 -> 157 us.
-// Two units per lane: 503 and 161 us.
+// rate is 6.7); fp32 -> bf16 at widths 1500 and 1721 (0.9 GB): 771 -> 157 us,
+// and 151 with the runs that the planner sends as vectors. Two units per lane:
+// 503 and 161 us.
 template <int kSs, int kDs>
 __device__ __forceinline__ void run_rows(const Task& t, const char* src, char* dst, uint32_t chunk) {
   constexpr int V = 16 / (kSs > kDs ? kSs : kDs);
