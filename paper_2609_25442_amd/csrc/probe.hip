@@ -1103,7 +1103,7 @@ int launch_diff2_batch(const DiffField* fields, const DiffTile* tiles, int64_t n
   const Sink<int64_t> out{index, value, capacity, count};
   // one held pass takes its tiles whole once there are a few times as many as
   // workgroups fit the chip: its int64 arithmetic bounds it, that of the halo
-  // rows too (7 GB of bf16 3570 us in strips, 3320 whole; 1.7 GB 470 and 483).
+  // rows too (14 GB of bf16 3570 us in strips, 3320 whole; 1.7 GB 470 and 483).
   // Two passes take strips at every size (28 GB of fp32 9.4 and 10.0 ms).
   const bool cut = cut_tiles(strips, ntiles) && (passes > 1 || ntiles < kWholeTiles);
   const dim3 grid(static_cast<unsigned>(cut ? ntiles * kTileParts : ntiles));
