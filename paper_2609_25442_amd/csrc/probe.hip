@@ -805,7 +805,7 @@ __device__ __forceinline__ TileShare tile_share(const DiffField* __restrict__ fi
   if (!kCut) return {int64_t(k), 0, true};
   const DiffField& f = fields[t.field];
   if (f.kind != DIFF_VEC && f.kind != DIFF_RAGGED) return {int64_t(k), int(b % kTileParts), true};
-  const unsigned per = unsigned(tile_grid(f).per_strip()), first = k - unsigned(t.j0) / kThreads;
+  const unsigned per = unsigned(tile_grid(f).per_strip()), first = k - unsigned(t.j0 / kThreads);
   const unsigned r = b - first * kTileParts, part = r / per, col = r - part * per;
   t.j0 = int64_t(col) * kThreads;
   return {int64_t(first + col), int(part), false};
