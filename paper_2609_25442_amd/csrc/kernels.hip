@@ -527,15 +527,23 @@ __global__ __launch_bounds__(kThreads) void wb_tasks_kernel(const Task* __restri
 // own words. Bound: HBM, one workgroup (16 waves) per CU by its LDS. 4-byte
 // tiles took the fp32 pack of a TP4 rank of half an 8 B dense model (2.4 of
 // its 9.1 GB transposed) from 1.64 (LDS tiles of 32 x 32) to 1.42 ms (6.4 TB/s).
-template <int kEs>
+// Launches of few 4-byte tiles (kPlainTiles, 256 MiB read and written) go without
+// the non-temporal hint: their data may be in the 256 MB cache, where the hint
+// cost a quarter (8 x 1000 x 4096: 71 us with it, 53 without; LDS tiles of 32 x
+// 32, which these replaced, 50-72). Larger launches are 4 % faster with it (24 x
+// 4096 x 4096: 533 and 553).
+constexpr uint32_t kPlainTiles = 1024;
+
+template <int kEs, bool kNt>
 __device__ __forceinline__ void run_tile(const Task& t, const char* src, char* dst, u32x4* lds) {
   constexpr int V = 16 / kEs, GC = kTileCols * 2 / 16;  // elements per word, words per source row
   constexpr int GR = kTileRows / V, H = 8 / V;          // words per destination row, words a thread gives each
   const int cg = threadIdx.x % GC, rg = threadIdx.x / GC;
+  const auto fetch = [](const u32x4* p) { return kNt ? ld(p) : *p; };
   u32x4 a[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
-    a[i] = ld(reinterpret_cast<const u32x4*>(src + (uint64_t(8 * rg + i) * t.src_ld + V * cg) * kEs));
+    a[i] = fetch(reinterpret_cast<const u32x4*>(src + (uint64_t(8 * rg + i) * t.src_ld + V * cg) * kEs));
 #pragma unroll
   for (int j = 0; j < V; ++j) {
     u32x4* row = lds + (V * cg + j) * GR;  // destination row V cg + j
@@ -549,11 +557,15 @@ __device__ __forceinline__ void run_tile(const Task& t, const char* src, char* d
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const int row = r0 + (kTileThreads / GR) * k;
-    st(lds[row * GR + (w ^ ((row / V) & (GR - 1)))],
-       reinterpret_cast<u32x4*>(dst + (uint64_t(row) * t.dst_ld + V * w) * kEs));
+    u32x4* p = reinterpret_cast<u32x4*>(dst + (uint64_t(row) * t.dst_ld + V * w) * kEs);
+    if (kNt)
+      st(lds[row * GR + (w ^ ((row / V) & (GR - 1)))], p);
+    else
+      *p = lds[row * GR + (w ^ ((row / V) & (GR - 1)))];
   }
 }
 
+template <bool kPlain>
 __global__ __launch_bounds__(kTileThreads) void wb_tile_kernel(const Task* __restrict__ tasks,
                                                                const uint64_t* __restrict__ ptrs, const char* buf,
                                                                const char* aux) {
@@ -562,9 +574,9 @@ __global__ __launch_bounds__(kTileThreads) void wb_tile_kernel(const Task* __res
   const char* src = base_of(t.src_idx, ptrs, buf, aux) + t.src_off;
   char* dst = const_cast<char*>(base_of(t.dst_idx, ptrs, buf, aux)) + t.dst_off;
   if (t.sdt == WB_F32)
-    run_tile<4>(t, src, dst, lds);
+    run_tile<4, !kPlain>(t, src, dst, lds);
   else
-    run_tile<2>(t, src, dst, lds);
+    run_tile<2, true>(t, src, dst, lds);
 }
 
 // ---- fp8 E4M3FN blocks ---------------------------------------------------
@@ -1220,7 +1232,8 @@ int launch_tasks(const Task* tasks, uint32_t n, const TaskSplit& sp, const uint6
     if (e != hipSuccess) return e;
   }
   if (sp.tiles) {
-    hipLaunchKernelGGL(wb_tile_kernel, dim3(sp.tiles), dim3(kTileThreads), 0, static_cast<hipStream_t>(stream),
+    const auto kernel = sp.tiles <= kPlainTiles ? wb_tile_kernel<true> : wb_tile_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(sp.tiles), dim3(kTileThreads), 0, static_cast<hipStream_t>(stream),
                        tasks + (n - sp.tiles), ptrs, static_cast<const char*>(buf), static_cast<const char*>(aux));
     return hipGetLastError();
   }

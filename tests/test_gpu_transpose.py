@@ -5,13 +5,14 @@ tile, packing and assembling, bit for bit against the oracle."""
 
 import numpy as np
 import pytest
+import torch
 
 import synthetic_checkpoint as sc
 import paper_2609_25442_amd as wb
 from oracle.catalog import CkptTensor
 from oracle.layout import Layout, Local, Placement, RankLayout
 
-from gpu_util import roundtrip
+from gpu_util import roundtrip, workspace_for
 from wb_cases import to_wb
 
 pytestmark = pytest.mark.gpu
@@ -50,3 +51,23 @@ def test_transposed_rollout(ra, rb, cols, tdt, rdt):
     ro = Layout(cat, [RankLayout([Local("x", rdt, 1, cols, W)],
                                  [Placement(0, 0, ra, 0, cols, 0, 0, W, 1), Placement(1, 0, rb, 0, cols, 0, ra, W, 1)])])
     roundtrip(tr, ro, _values(cat, tdt), label=f"ro-{tdt}-{rdt}-{ra}+{rb}x{cols}")
+
+
+@pytest.mark.parametrize("rows,cols", [(4096, 8192), (4096, 8448)])
+def test_fp32_tiles_on_both_sides_of_the_cache_rule(rows, cols):
+    """1024 tiles of 128 x 256 fp32 elements, the most that go without the
+    non-temporal hint, and 1056."""
+    L = wb.Layout.create([("T", rows, cols)], 1)
+    L.add_local(0, "t", "f32", 1, rows, cols)
+    L.add_placement(0, 0, 0, rows, 0, cols, 0, 0, cols)
+    R = wb.Layout.create([("T", rows, cols)], 1)
+    R.add_local(0, "x", "f32", 1, cols, rows)
+    R.add_placement(0, 0, 0, rows, 0, cols, 0, 0, rows, 1)
+    p = wb.Plan(L, R, wb.RECEIVER, 0)
+    assert p.launch_grid(4)[0] == rows // 128 * (cols // 256)
+    p.upload(workspace_for(p))
+    x = torch.randn(rows, cols, device="cuda")
+    out = wb.allocate_locals(R, 0)
+    p.unpack(x.view(-1), out)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], x.t())
